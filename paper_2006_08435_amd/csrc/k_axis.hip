@@ -4,27 +4,34 @@
 
 namespace fft3d {
 
-// Sum of n FP64 partials in a fixed order (one workgroup of 256 threads).
-__global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__ p, long n, double* __restrict__ out)
+// Sum of n FP64 partials in a fixed order, by one workgroup.  It is bound by
+// the latency of its loads, so every thread keeps four running sums over
+// loads that do not wait for each other, and 1024 threads share the list: the
+// 18432 partials of 128 x 96^3 took 19 us with 256 threads and one sum each.
+constexpr int kSumThreads = 1024;
+__global__ void __launch_bounds__(kSumThreads)
+k_sum_partials(const double* __restrict__ p, long n, double* __restrict__ out)
 {
-    __shared__ double red[256];
+    __shared__ double red[kSumThreads / 64];
     const int tid = threadIdx.x;
-    double s = 0.0;
-    for (long i = tid; i < n; i += 256) s += p[i];
-    red[tid] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (tid < o) red[tid] += red[tid + o];
-        __syncthreads();
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    long i = tid;
+    for (; i + 3 * kSumThreads < n; i += 4 * kSumThreads) {
+        s0 += p[i];
+        s1 += p[i + kSumThreads];
+        s2 += p[i + 2 * kSumThreads];
+        s3 += p[i + 3 * kSumThreads];
     }
-    if (tid == 0) out[0] = red[0];
+    for (; i < n; i += kSumThreads) s0 += p[i];
+    const double t = block_sum<kSumThreads>((s0 + s1) + (s2 + s3), red, tid);
+    if (tid == 0) out[0] = t;
 }
 
 long axis_str_blocks(long lines) { return (lines + kAxisLines - 1) / kAxisLines; }
 
 hipError_t launch_sum_partials(const double* partials, long n, double* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, st, partials, n, out);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kSumThreads), 0, st, partials, n, out);
     return hipGetLastError();
 }
 

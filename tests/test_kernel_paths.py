@@ -1,0 +1,42 @@
+"""Edge sizes of the kernels that a dispatch rule chooses between: remainders
+of tiles and loops, the smallest and the largest sizes of each rule, against
+the FP64 oracle.
+
+Bars: relative L2 <= 5e-6 for FP32 transforms and operators; a sum of
+non-negative FP32 products in FP64 to 1e-6 relative.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-6
+INVERSE, FORWARD = 1, -1
+
+
+@pytest.fixture(scope="module")
+def F():
+    import paper_2006_08435_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+def rel(a, b):
+    a = np.asarray(a, np.complex128).ravel()
+    b = np.asarray(b, np.complex128).ravel()
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+@pytest.mark.parametrize("b", [1, 1023, 1025, 3073, 4096, 4097, 9001])
+def test_sum_of_partials(F, b):
+    """One partial per 8 x 8 x 1 grid: every remainder of the sum's loops."""
+    c = workloads.uniform_grid((8, 8, 1), 100 + b, batch=b)
+    V = (workloads.uniform_grid((8, 8, 1), 99).real + 2.0).astype(np.float32)
+    E = F.energy(torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda()).item()
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    want = float((V.astype(np.float64) * np.abs(psi) ** 2).sum())
+    assert abs(E - want) <= 1e-6 * want
