@@ -157,7 +157,7 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
     // the tables are tiny and separate offsets keep the exec path simple).
     std::vector<float2> tab;
     const int kind = q16 ? 1 : 0;
-    auto append = [&](int n, int sign) {
+    auto append = [&](int n, int sign, int kind) {
         const long off = (long)tab.size();
         std::vector<float2> t = twiddles(n, sign, kind);
         tab.insert(tab.end(), t.begin(), t.end());
@@ -165,12 +165,13 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
         if (tab.size() % 2) tab.push_back(make_float2(0.f, 0.f));
         return off;
     };
-    p->tw_x = append(nx, direction);
-    p->tw_y = append(ny, direction);
-    p->tw_z = append(nz, direction);
-    p->tw_rx = append(nx, -direction);
-    p->tw_ry = append(ny, -direction);
-    p->tw_rz = append(nz, -direction);
+    p->tw_x = append(nx, direction, kind);
+    p->tw_y = append(ny, direction, kind);
+    p->tw_z = append(nz, direction, kind);
+    p->tw_rx = append(nx, -direction, kind);
+    p->tw_ry = append(ny, -direction, kind);
+    p->tw_rz = append(nz, -direction, kind);
+    if (nx == ny && !q16 && !large) p->tw_zrev = append(nz, FFT3D_FORWARD, 3);
     if (tab.empty()) tab.push_back(make_float2(0.f, 0.f));
     const size_t bytes = tab.size() * sizeof(float2);
     if (test_fail_alloc() || hipMalloc((void**)&p->d_tw, bytes) != hipSuccess) {
@@ -572,7 +573,7 @@ static hipError_t hloc_run(const fft3d_plan_s* p, const float2* c, float2* out, 
     const float2* twx_inv = p->d_tw + (inv_plan ? p->tw_x : p->tw_rx);
     const float2* twx_fwd = p->d_tw + (inv_plan ? p->tw_rx : p->tw_x);
     const float2* twz_inv = p->d_tw + (inv_plan ? p->tw_z : p->tw_rz);
-    const float2* twz_fwd = p->d_tw + (inv_plan ? p->tw_rz : p->tw_z);
+    const float2* twz_fwd = p->d_tw + p->tw_zrev;
     const AxisMap zmap{(long)p->batch * p->ny * n, n, p->ny, p->vol, (long)n, (long)n * p->ny};
     double* partials = E ? p->partials : nullptr;
     hipError_t e;

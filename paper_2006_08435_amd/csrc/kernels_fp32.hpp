@@ -1208,13 +1208,21 @@ k_axis_energy(const float2* in, const float2* __restrict__ tw, AxisMap m, const 
 // The z part of the local-potential operator of a plane-wave code,
 // out = forward(V * inverse(c)) with the transforms split as [inverse xy
 // planes] [this kernel] [forward xy planes]: each workgroup takes L adjacent
-// z-lines of the intermediate `buf`, runs the inverse z-transform into LDS
-// (psi of those lines, which never reaches HBM), accumulates sum V |psi|^2
-// (one FP64 partial per workgroup), multiplies psi by s V with
-// s = mult * (scale ? scale[0] : 1), runs the forward z-transform and stores
-// in place.  MODE 1 (sphere cutoff R2): only the elements with Gz^2 < R2 are
-// loaded (the others were never written by the pruned inverse plane pass)
-// and stored (the pruned forward plane pass reads only those planes).
+// z-lines of the intermediate `buf`, runs the inverse z-transform (psi of
+// those lines, which never reaches HBM), accumulates sum V |psi|^2 (one FP64
+// partial per workgroup, the products and their order those of the ENERGY
+// form of k_axis_str), multiplies psi by s V with s = mult * (scale ?
+// scale[0] : 1), runs the forward z-transform and stores in place.  MODE 1
+// (sphere cutoff R2): only the elements with Gz^2 < R2 are loaded (the others
+// were never written by the pruned inverse plane pass) and stored (the pruned
+// forward plane pass reads only those planes).
+// The forward transform runs the radices in the opposite order (kind 3,
+// tw_fwd is its table), so its first butterflies take psi from the registers
+// of the inverse's last ones, and the product with V lies between the two:
+// two LDS round trips per value instead of four, and for a single-stage
+// length none.  The kernel is bound by its butterflies and LDS sweeps more
+// than by HBM: with four round trips the z part of 64 x 90^3 with a cutoff
+// took 188 us, so 127 us (H psi from packed coefficients 604 -> 544 us).
 template <int N, int L, int MODE>
 __global__ void __launch_bounds__((AxisGeom<N, L>::T))
 k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __restrict__ tw_fwd, AxisMap m,
@@ -1223,9 +1231,13 @@ k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __rest
 {
     using G = AxisGeom<N, L>;
     using P = Plan1D<N>;
-    constexpr int T = G::T;
-    static_assert(T % L == 0, "each thread keeps one line");
-    __shared__ float2 lds[G::WORDS];
+    using Q = Plan1D<N, 3>;
+    constexpr int T = G::T, ST = P::stages - 1;
+    constexpr int R = P::radix(ST), M = N / R, NB = L * M, IT = (NB + T - 1) / T;   // last inverse = first forward
+    static_assert(T % L == 0 && L % 64 == 0 && T % 64 == 0, "each thread keeps one line, each wave one butterfly index");
+    static_assert(Q::radix(0) == R && P::ns(ST) == M, "the forward stage reads what the inverse stage writes");
+    static_assert(ST <= 3, "at most four stages");
+    __shared__ float2 lds[ST > 0 ? G::WORDS : 1];
     __shared__ double red[T / 64];
     const int tid = threadIdx.x;
     const long tile = rev_tile();
@@ -1251,35 +1263,78 @@ k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __rest
         dst = Out{buf + gbase, buf + gbase, m.es};
     }
     const LdsAcc<1, G::LP> a{lds};
-    // inverse z-transform into LDS
-    fft_stage<N, 0, 1, L, T, true, false>(src, a, tw_inv, tid, valid);
-    __syncthreads();
-    if constexpr (P::stages > 1) {
-        run_tail<N, 1, L, T, 1, false>(a, a, tw_inv, tid, valid);
-        __syncthreads();
-    }
-    // psi -> energy partial, s V psi
-    const float s = mult * (scale ? (float)scale[0] : 1.f);
-    double acc = 0.0;
-    if (myline < valid) {
-        const float* v = V + (gbase % vol);
-        for (int e = tid / L; e < N; e += T / L) {
-            const float2 p = lds[e * G::LP + myline];
-            const float vv = v[(long)e * m.es];
-            acc += (double)(vv * fmaf(p.x, p.x, p.y * p.y));
-            const float f = s * vv;
-            lds[e * G::LP + myline] = make_float2(f * p.x, f * p.y);
+    // V at this thread's points, in flight while the first stages run
+    const float* __restrict__ v = V + (gbase % vol);
+    float f[IT][R];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int b = tid + it * T, j = __builtin_amdgcn_readfirstlane(b / L);
+        if ((NB % T == 0 || b < NB) && myline < valid) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) f[it][q] = v[(long)(j + q * M) * m.es];
         }
     }
-    const double t = block_sum<T>(acc, red, tid);   // contains the barrier before the forward stages
-    if (tid == 0 && partials) partials[tile] = t;
-    // forward z-transform, stored in place
-    if constexpr (P::stages == 1) {
-        fft_stage<N, 0, -1, L, T, true, false>(a, dst, tw_fwd, tid, valid);
-    } else {
-        fft_stage<N, 0, -1, L, T, true, true>(a, a, tw_fwd, tid, valid);
+    // inverse z-transform but for its last stage
+    if constexpr (ST > 0) { fft_stage<N, 0, 1, L, T, true, false>(src, a, tw_inv, tid, valid); __syncthreads(); }
+    if constexpr (ST > 1) { fft_stage<N, 1, 1, L, T, true, true>(a, a, tw_inv, tid, valid); __syncthreads(); }
+    if constexpr (ST > 2) { fft_stage<N, 2, 1, L, T, true, true>(a, a, tw_inv, tid, valid); __syncthreads(); }
+    // last inverse stage -> psi -> energy partial, s V psi -> first forward stage
+    const float s = mult * (scale ? (float)scale[0] : 1.f);
+    const float2* __restrict__ tws = tw_inv + P::tw_off(ST);
+    double acc = 0.0;
+    float2 r[IT][R];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int b = tid + it * T;
+        const int j = __builtin_amdgcn_readfirstlane(b / L);
+        if ((NB % T == 0 || b < NB) && myline < valid) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                if constexpr (ST > 0) r[it][q] = a.load(myline, j + q * M);
+                else r[it][q] = src.load(myline, j + q * M);
+            }
+            if constexpr (ST > 0) {
+                const float2* __restrict__ w = tws + j * (R - 1);
+#pragma unroll
+                for (int q = 1; q < R; ++q) r[it][q] = cmul(r[it][q], w[q - 1]);
+            }
+            dft<R, 1>(r[it]);
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const float2 p = r[it][q];
+                acc += (double)(f[it][q] * fmaf(p.x, p.x, p.y * p.y));
+                const float g = s * f[it][q];
+                r[it][q] = make_float2(g * p.x, g * p.y);
+            }
+            dft<R, -1>(r[it]);
+        }
+    }
+    if (partials) {   // uniform
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = acc;
+    }
+    __syncthreads();   // every read of the tile is done; the waves' sums are visible
+    if (partials && tid == 0) {
+        double t = 0.0;
+        for (int w = 0; w < T / 64; ++w) t += red[w];
+        partials[tile] = t;
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int b = tid + it * T, j = b / L;
+        if ((NB % T == 0 || b < NB) && myline < valid) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                if constexpr (ST > 0) a.store(myline, j * R + q, r[it][q]);
+                else dst.store(myline, j * R + q, r[it][q]);
+            }
+        }
+    }
+    // the other forward stages, the last one stored in place in global memory
+    if constexpr (ST > 0) {
         __syncthreads();
-        run_tail<N, -1, L, T, 1, false>(a, dst, tw_fwd, tid, valid);
+        run_tail<N, -1, L, T, 1, false, 3>(a, dst, tw_fwd, tid, valid);
     }
 }
 

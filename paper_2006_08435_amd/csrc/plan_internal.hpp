@@ -75,6 +75,7 @@ struct fft3d_plan_s {
     float2* d_tw;              // all tables of the plan, one allocation
     long tw_x, tw_y, tw_z;     // offsets (elements) of each dimension's table
     long tw_rx, tw_ry, tw_rz;  // the same tables for the opposite sign
+    long tw_zrev;              // z table of sign -1, radices reversed (nx == ny FP32 plans: k_axis_hloc)
     long vol;
     double* partials;          // energy: one FP64 partial per z-pass workgroup (nx == ny plans)
     long n_partials;

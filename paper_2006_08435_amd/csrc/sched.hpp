@@ -154,11 +154,23 @@ __host__ __device__ constexpr Sched make_sched_alt(int n)
     }
 }
 
+// The default's radices in the opposite order (kind 3).  Its first stage reads
+// the elements j + q*N/R that the default's last stage, of the same radix R,
+// writes, so a transform of kind 3 can follow one of kind 0 in registers.
+__host__ __device__ constexpr Sched make_sched_rev(int n)
+{
+    const Sched t = make_sched(n);
+    Sched s{t.count, {0, 0, 0, 0, 0, 0, 0, 0}};
+    for (int i = 0; i < t.count; ++i) s.r[i] = t.r[t.count - 1 - i];
+    return s;
+}
+
 // kind 0: default; 1: radix 16 first (reduced-precision form); 2: the
-// autotuner's alternative order.
+// autotuner's alternative order; 3: the default order reversed.
 __host__ __device__ constexpr Sched make_sched_kind(int n, int kind)
 {
-    return kind == 1 ? make_sched16(n) : (kind == 2 ? make_sched_alt(n) : make_sched(n));
+    return kind == 1 ? make_sched16(n)
+                     : (kind == 2 ? make_sched_alt(n) : (kind == 3 ? make_sched_rev(n) : make_sched(n)));
 }
 
 __host__ __device__ constexpr int sched_ns(const Sched& s, int stage)

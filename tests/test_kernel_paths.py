@@ -40,3 +40,31 @@ def test_sum_of_partials(F, b):
     psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
     want = float((V.astype(np.float64) * np.abs(psi) ** 2).sum())
     assert abs(E - want) <= 1e-6 * want
+
+
+@pytest.mark.parametrize("nz", [1, 2, 3, 15, 16, 18, 20, 75, 81, 100, 108, 120, 125])
+@pytest.mark.parametrize("cut", [False, True])
+def test_operator_lengths(F, nz, cut):
+    """The fused z kernel of the operator at one-, two- and three-stage
+    lengths, 10 x 10 lines a grid: the last tile of 64 lines is ragged."""
+    n, b = 10, 3
+    r2 = 2.5 ** 2
+    gz = workloads.signed_freq(nz)[:, None, None]
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + gz ** 2) < r2
+    c = workloads.uniform_grid((n, n, nz), 300 + nz, batch=b)
+    if cut:
+        c = (c * inside).astype(np.complex64)
+    V = (workloads.uniform_grid((n, n, nz), 400 + nz).real + 1.5).astype(np.float32)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    if cut:
+        plan.set_cutoff(r2)
+    E = torch.zeros((), dtype=torch.float64, device="cuda")
+    scale = torch.tensor(-0.5, dtype=torch.float64, device="cuda")
+    out = plan.apply_potential(torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda(), E=E, scale=scale).cpu().numpy()
+    want = -0.5 * oracle.apply_potential(c.astype(np.complex128), V.astype(np.float64))
+    if cut:
+        out, want = out[:, inside], want[:, inside]
+    assert rel(out, want) <= TOL
+    E_ref, _, _ = oracle.energy(c.astype(np.complex128), V.astype(np.float64), want_grad=False)
+    assert abs(E.item() - E_ref) <= 1e-6 * abs(E_ref)
