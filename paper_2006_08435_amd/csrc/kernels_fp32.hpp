@@ -25,20 +25,41 @@ constexpr int odd_stride(int n) { return (n % 2 == 0) ? n + 1 : n; }
 
 constexpr int round_up(int a, int m) { return (a + m - 1) / m * m; }
 
-// Threads for a tile of `lines` transforms of length N: one butterfly of the
-// largest radix per thread, clamped to [64, 1024].
+// Threads for a tile of `lines` transforms of length N.  At least one
+// butterfly of the largest radix per thread (T0); above that, the count whose
+// stages leave the fewest lanes idle: a stage of radix R has lines * N / R
+// butterflies and takes ceil of that over T turns of about R steps each, and
+// a last turn that only a few waves take holds the others at the barrier.
+// At 90 = 10 * 9 one wave of nine had a second radix-9 butterfly.  Only from
+// six waves on: smaller workgroups share a compute unit with five or more
+// others, which hide the idle turn, and more waves each would only let fewer
+// of them in (planes of 40 with 320 threads instead of 256: 300 grids of 40^3
+// inverse + forward 206 -> 219 us).  What changes up to 128 points: planes of
+// 54, 80 and 90, z tiles of 80, 90 and 108.  Inverse + forward, T0 -> this
+// count: 200 x 54^3 382 -> 348 us, 64 x 80^3 342 -> 336, 64 x 90^3 537 -> 531,
+// 32 x 108^3 469 -> 446.  Above 128 points the same count measured both ways
+// (8 x 180^3 877 -> 901 us, 8 x 192^3 996 -> 974); those tiles keep T0.
+template <int N, int KIND = 0>
+constexpr int threads_for_kind(int lines)
+{
+    using P = Plan1D<N, KIND>;
+    int t0 = round_up(lines * N / P::max_radix, 64);
+    t0 = t0 < 64 ? 64 : (t0 > 1024 ? 1024 : t0);
+    auto turns = [lines](int t) {
+        int c = 0;
+        for (int s = 0; s < P::stages; ++s) c += (lines * (N / P::radix(s)) + t - 1) / t * P::radix(s);
+        return (long)c * t;   // thread-steps: the useful ones are the same for every t
+    };
+    int best = t0;
+    for (int t = t0 + 64; N <= 128 && t0 >= 384 && t <= 1024; t += 64)
+        if (turns(t) < turns(best)) best = t;
+    return best;
+}
+
 template <int N>
 constexpr int threads_for(int lines)
 {
-    int t = round_up(lines * N / Plan1D<N>::max_radix, 64);
-    return t < 64 ? 64 : (t > 1024 ? 1024 : t);
-}
-
-template <int N, int KIND>
-constexpr int threads_for_kind(int lines)
-{
-    int t = round_up(lines * N / Plan1D<N, KIND>::max_radix, 64);
-    return t < 64 ? 64 : (t > 1024 ? 1024 : t);
+    return threads_for_kind<N>(lines);
 }
 
 // 2D LDS accessor: line -> (hi, lo) = (line / LDIV, line % LDIV);
