@@ -46,7 +46,7 @@ KERNEL_UNITS = {
     "k_plane_pf": ("k_plane.hip", "k_variants.hip"), "k_plane_pruned": ("k_plane.hip",),
     "k_axis_str": ("k_axis.hip", "k_axis_large.hip", "k_variants.hip"), "k_axis_row": ("k_axis.hip", "k_axis_large.hip"),
     "k_axis_density": ("k_axis.hip",), "k_axis_energy": ("k_axis.hip",), "k_axis_hloc": ("k_axis.hip",),
-    "k_sum_partials": ("k_axis.hip",), "k_sphere_copy": ("k_axis.hip",), "k_fused_xcd": ("k_fused.hip",),
+    "k_sum_partials": ("k_axis.hip",), "k_sphere_": ("k_axis.hip",), "k_fused_xcd": ("k_fused.hip",),
     "k_many": ("k_many.hip",), "k_plane_r2c": ("k_real.hip",), "k_plane_c2r": ("k_real.hip",),
     "k_stream_copy": ("k_copy.hip",), "k_q16_": ("k_q16.hip",),
 }

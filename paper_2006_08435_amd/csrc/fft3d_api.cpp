@@ -830,16 +830,35 @@ long long fft3d_plan_sphere_points(fft3d_plan_t p)
     return p->sphere_pts;
 }
 
+// The sphere's extent along an axis of n points.
+static SphereAxis sphere_axis(int n, double r2)
+{
+    SphereAxis a{n, 0, 0};
+    for (int k = 0; k < n; ++k) {
+        const int g = signed_freq(k, n);
+        if ((double)(g * g) < r2) ++(g >= 0 ? a.npos : a.nneg);
+    }
+    return a;
+}
+
+static hipError_t sphere_pack(const fft3d_plan_s* p, const float2* dense, float2* packed, hipStream_t st)
+{
+    return launch_sphere_pack(dense, packed, p->d_rows, p->sphere_pts, p->d_zlist, p->n_zlist, p->nz,
+                              sphere_axis(p->nx, p->cut_r2), sphere_axis(p->ny, p->cut_r2), p->batch, st);
+}
+
 static int sphere_copy(fft3d_plan_t p, bool pack, const void* src, void* dst, fft3d_stream_t stream)
 {
     const int rc = check_ptrs(p, src, dst);
     if (rc != FFT3D_OK) return rc;
     if (p->cut_r2 <= 0 || p->many) return FFT3D_E_UNSUPPORTED;
     if (src == dst) return FFT3D_E_INVALID_ARG;
-    const long total = (long)p->batch * p->vol;
-    const hipError_t e = launch_sphere_copy(pack, static_cast<const float2*>(src), static_cast<float2*>(dst), p->d_rows,
-                                            p->sphere_pts, p->nx, (long)p->nz * p->ny, total,
-                                            reinterpret_cast<hipStream_t>(stream));
+    const float2* s = static_cast<const float2*>(src);
+    float2* d = static_cast<float2*>(dst);
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    const hipError_t e = pack ? sphere_pack(p, s, d, st)
+                              : launch_sphere_unpack(s, d, p->d_rows, p->sphere_pts, p->nz, p->ny, p->nx, p->cut_r2,
+                                                     p->batch, st);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return FFT3D_E_LAUNCH;
@@ -883,8 +902,7 @@ int fft3d_exec_packed(fft3d_plan_t p, void* dense, void* packed, fft3d_stream_t 
                 const Pass& z = p->passes[1];
                 e = axis_str_pruned_fn(z.n, S)(d, pk, p->d_tw + z.tw, z.map, p->cut_r2, p->d_rows, p->sphere_pts, st);
             } else {
-                e = launch_sphere_copy(true, d, pk, p->d_rows, p->sphere_pts, p->nx, (long)p->nz * p->ny,
-                                       (long)p->batch * p->vol, st);
+                e = sphere_pack(p, d, pk, st);
             }
         }
     }

@@ -143,18 +143,31 @@ DensityFn axis_density_fn(int n)
     }
 }
 
-hipError_t launch_sphere_copy(bool pack, const float2* src, float2* dst, const SphereRow* rows, long npts, int nx,
-                              long nyz, long total, hipStream_t st)
+// Workgroups of the packed-sphere copies: one per plane, four waves where the
+// plane has more than two waves' worth of points; grid-stride beyond 2^20.
+static dim3 sphere_grid(long planes) { return dim3((unsigned)(planes < (1L << 20) ? planes : (1L << 20))); }
+static dim3 sphere_block(long points) { return dim3(points > 128 ? 256 : 64); }
+
+hipError_t launch_sphere_pack(const float2* src, float2* dst, const SphereRow* rows, long npts, const int* zlist,
+                              int nzp, int nz, const SphereAxis& ax, const SphereAxis& ay, long batch, hipStream_t st)
 {
-    if (total <= 0) return hipSuccess;
-    long blocks = (total + 255) / 256;
-    if (blocks > 8192) blocks = 8192;   // grid-stride beyond 2M points
-    if (pack)
-        hipLaunchKernelGGL((k_sphere_copy<true>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, npts, nx,
-                           nyz, total);
+    const long planes = batch * nzp;
+    if (planes <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_sphere_pack, sphere_grid(planes), sphere_block((long)ax.count() * ay.count()), 0, st, src,
+                       dst, rows, npts, zlist, nzp, nz, ax, ay, planes);
+    return hipGetLastError();
+}
+
+hipError_t launch_sphere_unpack(const float2* src, float2* dst, const SphereRow* rows, long npts, int nz, int ny,
+                                int nx, double R2, long batch, hipStream_t st)
+{
+    const long planes = batch * nz;
+    if (nx % 2 == 0)   // every row, so every plane, starts on 16 bytes
+        hipLaunchKernelGGL(k_sphere_unpack<2>, sphere_grid(planes), sphere_block((long)ny * nx / 2), 0, st, src, dst,
+                           rows, npts, nz, ny, nx, R2, planes);
     else
-        hipLaunchKernelGGL((k_sphere_copy<false>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, npts, nx,
-                           nyz, total);
+        hipLaunchKernelGGL(k_sphere_unpack<1>, sphere_grid(planes), sphere_block((long)ny * nx), 0, st, src, dst, rows,
+                           npts, nz, ny, nx, R2, planes);
     return hipGetLastError();
 }
 

@@ -10,6 +10,7 @@ struct AxisMap;
 struct FusedCtl;
 struct ManyArgs;
 struct SphereRow;
+struct SphereAxis;
 
 using CubeFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, long grids, hipStream_t st);
 using PlaneFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, long planes, hipStream_t st);
@@ -53,9 +54,12 @@ using PlanePrunedFn = hipError_t (*)(const float2* in, float2* out, const float2
                                      hipStream_t st);
 using AxisStrPrunedFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, const AxisMap& m, double R2,
                                        const SphereRow* rows, long npts, hipStream_t st);
-// Dense [batch][nz][ny][nx] <-> packed [batch][npts] (pack: gather, else scatter with zeros).
-hipError_t launch_sphere_copy(bool pack, const float2* src, float2* dst, const SphereRow* rows, long npts, int nx,
-                              long nyz, long total, hipStream_t st);
+// Dense [batch][nz][ny][nx] -> packed [batch][npts] (gather) and back (with
+// zeros outside the sphere).
+hipError_t launch_sphere_pack(const float2* src, float2* dst, const SphereRow* rows, long npts, const int* zlist,
+                              int nzp, int nz, const SphereAxis& ax, const SphereAxis& ay, long batch, hipStream_t st);
+hipError_t launch_sphere_unpack(const float2* src, float2* dst, const SphereRow* rows, long npts, int nz, int ny,
+                                int nx, double R2, long batch, hipStream_t st);
 PlanePrunedFn plane_pruned_fn(int n, int sign);
 // Forward plane pass over the planes of zlist storing only the sphere.
 PlanePrunedFn plane_ball_fwd_fn(int n);

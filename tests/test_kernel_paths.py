@@ -68,3 +68,22 @@ def test_operator_lengths(F, nz, cut):
     assert rel(out, want) <= TOL
     E_ref, _, _ = oracle.energy(c.astype(np.complex128), V.astype(np.float64), want_grad=False)
     assert abs(E.item() - E_ref) <= 1e-6 * abs(E_ref)
+
+
+@pytest.mark.parametrize("n,nz,b,r2", [(1, 1, 3, 1.0), (2, 3, 2, 0.5), (3, 2, 5, 1e9), (8, 8, 300, 4.0), (15, 4, 2, 14.0),
+                                       (16, 5, 3, 1e9), (90, 3, 2, 0.1), (90, 2, 2, 506.25), (125, 2, 1, 3844.0)])
+def test_sphere_copies(F, n, nz, b, r2):
+    """Spheres from the origin alone to every point, odd and even rows, planes
+    of less than a wave: data movement, so bit for bit."""
+    gz = workloads.signed_freq(nz)[:, None, None]
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + gz ** 2) < r2
+    x = workloads.uniform_grid((n, n, nz), 500 + n, batch=b)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    plan.set_cutoff(r2)
+    packed = plan.pack(torch.from_numpy(x).cuda())
+    assert np.array_equal(packed.cpu().numpy().view(np.uint64), x[:, inside].view(np.uint64))
+    dense = torch.full((b, nz, n, n), complex("nan"), dtype=torch.complex64, device="cuda")
+    got = plan.unpack(packed, dense).cpu().numpy()
+    want = np.where(inside[None], x, np.complex64(0))
+    assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
