@@ -361,6 +361,25 @@ int fft3d_energy(fft3d_plan_t plan, const void *c, const float *V, void *work, d
                  fft3d_stream_t stream);
 
 /*
+ * E together with the first half of its gradient, for callers that want both
+ * (a training step): the last pass of the inverse transform also multiplies
+ * psi_n by V and runs the forward z transform on it, so the gradient needs
+ * one more pass instead of two and psi is never written.
+ *   fft3d_energy_vpsi_fwd: E as fft3d_energy_fwd (the same products summed
+ *     in the same order), and vpsi (device, the size of c; vpsi == c allowed
+ *     and then overwrites c) = V psi_n transformed forward along z.
+ *   fft3d_energy_vpsi_bwd: grad_c = 2 gE_dev[0] * (vpsi transformed forward
+ *     along x and y) = the gradient of gE * E.  grad_c may equal vpsi.
+ * The forward transform runs z before xy, so the gradient agrees with
+ * fft3d_energy_bwd's to FP32 rounding.  Plans and return codes as for
+ * fft3d_energy_fwd.
+ */
+int fft3d_energy_vpsi_fwd(fft3d_plan_t plan, const void *c, const float *V, void *vpsi, double *E_dev,
+                          fft3d_stream_t stream);
+int fft3d_energy_vpsi_bwd(fft3d_plan_t plan, const void *vpsi, const double *gE_dev, void *grad_c,
+                          fft3d_stream_t stream);
+
+/*
  * fft3d_energy without allocation, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same E as fft3d_energy on a plan of `batch`

@@ -63,6 +63,8 @@ SIGNATURES = {
     "fft3d_plan_tune": (_ci, [_vp]),
     "fft3d_energy_fwd": (_ci, [_vp, _vp, _vp, _vp, _vp, _vp]),
     "fft3d_energy": (_ci, [_vp, _vp, _vp, _vp, _vp, _vp]),
+    "fft3d_energy_vpsi_fwd": (_ci, [_vp, _vp, _vp, _vp, _vp, _vp]),
+    "fft3d_energy_vpsi_bwd": (_ci, [_vp, _vp, _vp, _vp, _vp]),
     "fft3d_energy_bwd": (_ci, [_vp, _vp, _ci, _vp, _vp, _vp, _vp]),
     "fft3d_exec_pass": (_ci, [_vp, _ci, _vp, _vp, _vp]),
     "fft3d_energy_noalloc": (_ci, [_ci, _ci, _ci, _ci, _vp, _vp, _vp, _vp, _vp]),

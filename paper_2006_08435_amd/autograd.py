@@ -5,12 +5,15 @@
   other one, since the adjoint (conjugate transpose) of the unnormalised
   forward DFT is the unnormalised inverse.
 * LocalPotentialEnergy: E = sum_n sum_r V(r) |psi_n(r)|^2 with
-  psi_n = IFFT3D(c_n), computed by fft3d_energy_fwd (inverse transform with
-  the sum fused into its last pass); backward = fft3d_energy_bwd, i.e.
-  grad_c = FFT3D(2 gE V psi), with the 2 gE V factor fused into the first
-  pass.  With save_psi=False the forward is fft3d_energy (E only, psi never
-  written) and the backward recomputes psi inside the fused operator.  Gradients follow PyTorch's convention for real functions of complex
-  tensors: dE/dRe(c) + i dE/dIm(c).
+  psi_n = IFFT3D(c_n) and grad_c = FFT3D(2 gE V psi).  The forward is
+  fft3d_energy_vpsi_fwd: an inverse transform whose last pass sums E,
+  multiplies psi by V and runs the gradient's z transform on it; that product
+  is what the backward keeps (the memory of one psi), and fft3d_energy_vpsi_bwd
+  finishes it in one pass.  With save_psi=False, or when no gradient is
+  asked for, the forward is fft3d_energy (E only, nothing of psi written) and
+  the backward recomputes psi inside the fused operator.  Gradients follow
+  PyTorch's convention for real functions of complex tensors:
+  dE/dRe(c) + i dE/dIm(c).
 """
 from __future__ import annotations
 
@@ -57,17 +60,20 @@ class LocalPotentialEnergy(torch.autograd.Function):
         cb, Vc = _check_energy_args(c, V)
         b, nz, ny, nx = cb.shape
         plan = get_plan(nx, ny, nz, b, "fp32", FFT3D_INVERSE)
-        psi = torch.empty_like(cb)   # psi, or the intermediate of the E-only pass
+        # V psi transformed along z (the gradient's first half), or the
+        # intermediate of the E-only pass
+        psi = torch.empty_like(cb)
+        save_psi = bool(save_psi) and any(ctx.needs_input_grad)
         E = torch.empty((), dtype=torch.float64, device=cb.device)
         sh = int(torch.cuda.current_stream().cuda_stream)
         if save_psi:
-            _lib.check(_lib.lib().fft3d_energy_fwd(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
-                                                   E.data_ptr(), sh), "fft3d_energy_fwd")
+            _lib.check(_lib.lib().fft3d_energy_vpsi_fwd(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
+                                                        E.data_ptr(), sh), "fft3d_energy_vpsi_fwd")
         else:   # psi is recomputed by the backward: E alone, psi never written
             _lib.check(_lib.lib().fft3d_energy(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
                                                E.data_ptr(), sh), "fft3d_energy")
         ctx.save_for_backward(psi if save_psi else cb, Vc)
-        ctx.have_psi = bool(save_psi)
+        ctx.have_psi = save_psi
         ctx.squeeze = c.dim() == 3
         ctx.plan = plan
         return E
@@ -78,8 +84,12 @@ class LocalPotentialEnergy(torch.autograd.Function):
         grad = torch.empty_like(src)
         g64 = gE.detach().to(torch.float64).reshape(()).contiguous()
         sh = int(torch.cuda.current_stream().cuda_stream)
-        _lib.check(_lib.lib().fft3d_energy_bwd(ctx.plan.handle, src.data_ptr(), int(ctx.have_psi), Vc.data_ptr(),
-                                               g64.data_ptr(), grad.data_ptr(), sh), "fft3d_energy_bwd")
+        if ctx.have_psi:
+            _lib.check(_lib.lib().fft3d_energy_vpsi_bwd(ctx.plan.handle, src.data_ptr(), g64.data_ptr(),
+                                                        grad.data_ptr(), sh), "fft3d_energy_vpsi_bwd")
+        else:
+            _lib.check(_lib.lib().fft3d_energy_bwd(ctx.plan.handle, src.data_ptr(), 0, Vc.data_ptr(), g64.data_ptr(),
+                                                   grad.data_ptr(), sh), "fft3d_energy_bwd")
         if ctx.squeeze:
             grad = grad[0]
         return grad, None, None

@@ -601,6 +601,45 @@ static hipError_t hloc_run(const fft3d_plan_s* p, const float2* c, float2* out, 
     return e;
 }
 
+int fft3d_energy_vpsi_fwd(fft3d_plan_t p, const void* c, const float* V, void* vpsi, double* E_dev,
+                          fft3d_stream_t stream)
+{
+    const int rc = energy_args(p, c, vpsi, V, E_dev);
+    if (rc != FFT3D_OK) return rc;
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    const bool inv_plan = p->direction == FFT3D_INVERSE;
+    const int n = p->nx, nz = p->nz;
+    float2* out = static_cast<float2*>(vpsi);
+    hipError_t e = plane_pf_fn(n, FFT3D_INVERSE)(static_cast<const float2*>(c), out,
+                                                 p->d_tw + (inv_plan ? p->tw_x : p->tw_rx), (long)p->batch * nz,
+                                                 p->pf_grid, 0, nullptr, nullptr, nz, true, st);
+    const AxisMap zmap{(long)p->batch * p->ny * n, n, p->ny, p->vol, (long)n, (long)n * p->ny};
+    if (e == hipSuccess)
+        e = axis_hloc_fn(nz)(out, p->d_tw + (inv_plan ? p->tw_z : p->tw_rz), p->d_tw + p->tw_zrev, zmap, V, nullptr,
+                             1.0f, p->partials, p->vol, 0.0, 0, st);
+    if (e == hipSuccess) e = launch_sum_partials(p->partials, p->n_partials, E_dev, st);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return FFT3D_E_LAUNCH;
+    }
+    return FFT3D_OK;
+}
+
+int fft3d_energy_vpsi_bwd(fft3d_plan_t p, const void* vpsi, const double* gE_dev, void* grad_c, fft3d_stream_t stream)
+{
+    const int rc = energy_args(p, vpsi, grad_c, vpsi, gE_dev);
+    if (rc != FFT3D_OK) return rc;
+    const float2* twx = p->d_tw + (p->direction == FFT3D_INVERSE ? p->tw_rx : p->tw_x);
+    const hipError_t e = plane_pf_fn(p->nx, FFT3D_FORWARD)(
+        static_cast<const float2*>(vpsi), static_cast<float2*>(grad_c), twx, (long)p->batch * p->nz, p->pf_grid, 2,
+        nullptr, gE_dev, p->nz, false, reinterpret_cast<hipStream_t>(stream));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return FFT3D_E_LAUNCH;
+    }
+    return FFT3D_OK;
+}
+
 int fft3d_apply_potential(fft3d_plan_t p, const void* c, const float* V, void* out, double* E_dev,
                           const double* scale_dev, fft3d_stream_t stream)
 {

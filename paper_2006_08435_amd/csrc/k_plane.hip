@@ -16,21 +16,28 @@ static hipError_t launch_plane_pf(const float2* in, float2* out, const float2* t
                                   const float* V, const double* gE, int nz, bool stream, hipStream_t st)
 {
     const dim3 g((unsigned)grid), b(PlaneGeom<N>::T);
+    if (scale == 2) {   // its input was just written by the pass before it: no streaming
+        if constexpr (S < 0) {
+            hipLaunchKernelGGL((k_plane_pf<N, S, 2>), g, b, 0, st, in, out, tw, planes, V, gE, nz, 0L);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     if constexpr (stream_plane(N)) {
         constexpr long pb = (long)N * N * sizeof(float2);
         if (stream && planes * pb >= kStreamMinBytes) {
             const long ntp = streamed_store_planes(planes, pb);   // used where the stores are paired
             if (scale)
-                hipLaunchKernelGGL((k_plane_pf<N, S, true, true>), g, b, 0, st, in, out, tw, planes, V, gE, nz, ntp);
+                hipLaunchKernelGGL((k_plane_pf<N, S, 1, true>), g, b, 0, st, in, out, tw, planes, V, gE, nz, ntp);
             else
-                hipLaunchKernelGGL((k_plane_pf<N, S, false, true>), g, b, 0, st, in, out, tw, planes, V, gE, nz, ntp);
+                hipLaunchKernelGGL((k_plane_pf<N, S, 0, true>), g, b, 0, st, in, out, tw, planes, V, gE, nz, ntp);
             return hipGetLastError();
         }
     }
     if (scale)
-        hipLaunchKernelGGL((k_plane_pf<N, S, true>), g, b, 0, st, in, out, tw, planes, V, gE, nz, 0L);
+        hipLaunchKernelGGL((k_plane_pf<N, S, 1>), g, b, 0, st, in, out, tw, planes, V, gE, nz, 0L);
     else
-        hipLaunchKernelGGL((k_plane_pf<N, S, false>), g, b, 0, st, in, out, tw, planes, V, gE, nz, 0L);
+        hipLaunchKernelGGL((k_plane_pf<N, S>), g, b, 0, st, in, out, tw, planes, V, gE, nz, 0L);
     return hipGetLastError();
 }
 
@@ -38,7 +45,7 @@ template <int N>
 static int plane_pf_occ()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_plane_pf<N, -1, false>),
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_plane_pf<N, -1>),
                                                      PlaneGeom<N>::T, 0) != hipSuccess) {
         (void)hipGetLastError();
         return 1;

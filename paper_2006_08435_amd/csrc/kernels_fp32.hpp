@@ -221,6 +221,24 @@ struct TileRegs {
             }
         }
     }
+    // The tile times the real s.
+    template <int RS>
+    __device__ __forceinline__ void store_lds(float2* lds, int tid, float s) const
+    {
+#pragma unroll
+        for (int k = 0; k < IT; ++k) {
+            const int i = tid + k * T;
+            if (UNITS % T == 0 || i < UNITS) {
+                if constexpr (PAIRS) {
+                    const int e = 2 * i, row = e / ROW, col = e % ROW;
+                    lds[row * RS + col] = make_float2(s * r[k].x, s * r[k].y);
+                    lds[row * RS + col + 1] = make_float2(s * r[k].z, s * r[k].w);
+                } else {
+                    lds[(i / ROW) * RS + (i % ROW)] = make_float2(s * r[k].x, s * r[k].y);
+                }
+            }
+        }
+    }
     template <int RS>
     __device__ __forceinline__ void store_lds(float2* lds, int tid) const
     {
@@ -453,16 +471,17 @@ __device__ __forceinline__ void tail_pairs(const A& a, float2* out, long es, con
 // w, w + G, w + 2G, ... and loads plane p + G into registers while plane p is
 // being transformed, so HBM latency overlaps the LDS/VALU phases.
 //
-// SCALE: every input value at grid position r is first multiplied by the real
+// SCALE 1: every input value at grid position r is first multiplied by the real
 // factor 2 * gE[0] * V[r] (V: one [nz][N][N] grid shared by the batch) -- the
-// prologue of the energy gradient.
+// prologue of the energy gradient from a stored psi.  SCALE 2: by 2 * gE[0]
+// alone, the last pass of the gradient whose z part k_axis_hloc has done.
 // NT: streaming plane loads (see stream_plane); planes below nt_planes
 // (streamed_store_planes) also stream their stores, the rest keep the
 // default policy so that the z pass after it finds the last part of the
 // output in the caches.
 // K: schedule kind of both 1D transforms (0 default, 2 the tuner's
 // alternative order; the twiddle table must be of the same kind).
-template <int N, int S, bool SCALE = false, bool NT = false, int K = 0>
+template <int N, int S, int SCALE = 0, bool NT = false, int K = 0>
 __global__ void __launch_bounds__(PlaneGeom<N>::T)
 k_plane_pf(const float2* in, float2* out, const float2* __restrict__ tw, long planes, const float* __restrict__ V,
            const double* __restrict__ gE, int nz, long nt_planes)
@@ -483,20 +502,21 @@ k_plane_pf(const float2* in, float2* out, const float2* __restrict__ tw, long pl
     TileRegs<N, N, T, NT> regs;
     FactorRegs<N, N, T> vr;
     float scale = 0.f;
-    if constexpr (SCALE) scale = (float)(2.0 * gE[0]);
+    if constexpr (SCALE != 0) scale = (float)(2.0 * gE[0]);
     long p = blockIdx.x;
     if (p < planes) {
         regs.load(in + p * N * N, tid);
-        if constexpr (SCALE) regs.load_factors(vr, V + (p % nz) * N * N, tid);
+        if constexpr (SCALE == 1) regs.load_factors(vr, V + (p % nz) * N * N, tid);
     }
     for (; p < planes; p += gridDim.x) {
-        if constexpr (SCALE) regs.template store_lds_scaled<RS>(lds, tid, vr, scale);
+        if constexpr (SCALE == 1) regs.template store_lds_scaled<RS>(lds, tid, vr, scale);
+        else if constexpr (SCALE == 2) regs.template store_lds<RS>(lds, tid, scale);
         else regs.template store_lds<RS>(lds, tid);
         __syncthreads();
         const long pn = p + gridDim.x;
         if (pn < planes) {
             regs.load(in + pn * N * N, tid);
-            if constexpr (SCALE) regs.load_factors(vr, V + (pn % nz) * N * N, tid);
+            if constexpr (SCALE == 1) regs.load_factors(vr, V + (pn % nz) * N * N, tid);
         }
         fft_lds_all<N, S, N, T, RS, 1, K>(lds, tw, tid);
         if constexpr (pairs_ok<N, N, K>(T)) {   // y transform: lines = x, rows y N apart

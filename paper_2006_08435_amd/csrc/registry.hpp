@@ -14,7 +14,8 @@ struct SphereAxis;
 
 using CubeFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, long grids, hipStream_t st);
 using PlaneFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, long planes, hipStream_t st);
-// scale != 0: fused prologue, input at r multiplied by 2 gE[0] V[r].
+// scale 1: fused prologue, input at r multiplied by 2 gE[0] V[r]; 2 (sign -1):
+// by 2 gE[0].
 // stream: the input is cold (not just written by the pass before), so its
 // loads may stream (stream_plane, kStreamMinBytes).
 using PlanePfFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, long planes, int grid, int scale,

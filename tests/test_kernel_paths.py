@@ -87,3 +87,35 @@ def test_sphere_copies(F, n, nz, b, r2):
     got = plan.unpack(packed, dense).cpu().numpy()
     want = np.where(inside[None], x, np.complex64(0))
     assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
+
+
+@pytest.mark.parametrize("n,nz,b", [(2, 1, 1), (9, 16, 3), (25, 20, 3), (30, 75, 2), (45, 64, 2), (96, 12, 3), (128, 9, 3)])
+@pytest.mark.parametrize("direction", [INVERSE, FORWARD])
+def test_energy_with_half_gradient(F, n, nz, b, direction):
+    """E bit for bit as the form that stores psi, the gradient against the
+    oracle, out of place and with every buffer the same."""
+    lib = F._lib.lib()
+    c = workloads.uniform_grid((n, n, nz), 600 + n, batch=b)
+    V = (workloads.uniform_grid((n, n, nz), 700 + nz).real + 1.5).astype(np.float32)
+    plan = F.Plan(n, n, nz, b, "fp32", direction)
+    ct, Vt = torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda()
+    E = torch.zeros(2, dtype=torch.float64, device="cuda")
+    gE = torch.tensor(-0.75, dtype=torch.float64, device="cuda")
+    half, grad = torch.empty_like(ct), torch.empty_like(ct)
+    s = torch.cuda.current_stream().cuda_stream
+    assert lib.fft3d_energy_fwd(plan.handle, ct.data_ptr(), Vt.data_ptr(), half.data_ptr(), E[0:].data_ptr(), s) == 0
+    assert lib.fft3d_energy_vpsi_fwd(plan.handle, ct.data_ptr(), Vt.data_ptr(), half.data_ptr(), E[1:].data_ptr(),
+                                     s) == 0
+    assert lib.fft3d_energy_vpsi_bwd(plan.handle, half.data_ptr(), gE.data_ptr(), grad.data_ptr(), s) == 0
+    assert torch.equal(ct.cpu(), torch.from_numpy(c))
+    same = ct.clone()
+    assert lib.fft3d_energy_vpsi_fwd(plan.handle, same.data_ptr(), Vt.data_ptr(), same.data_ptr(), E[1:].data_ptr(),
+                                     s) == 0
+    assert lib.fft3d_energy_vpsi_bwd(plan.handle, same.data_ptr(), gE.data_ptr(), same.data_ptr(), s) == 0
+    assert E[0].item() == E[1].item()
+    _, _, want = oracle.energy(c.astype(np.complex128), V.astype(np.float64))
+    assert rel(grad.cpu().numpy(), -0.75 * want) <= TOL
+    assert torch.equal(same, grad)
+    assert lib.fft3d_energy_vpsi_fwd(plan.handle, ct.data_ptr() + 8, Vt.data_ptr(), half.data_ptr(), E.data_ptr(),
+                                     s) == -6
+    assert lib.fft3d_energy_vpsi_bwd(plan.handle, half.data_ptr(), None, grad.data_ptr(), s) == -1
