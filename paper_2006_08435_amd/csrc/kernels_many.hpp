@@ -67,13 +67,36 @@ constexpr int many_lds_need()
     return many_per<N, T>() * PlaneGeom<N>::WORDS;
 }
 
+// A pointer that every lane holds alike, as a scalar: arguments of an
+// out-of-line function arrive in vector registers and as generic pointers.
+// With the value read from the first lane and its address space (1 global,
+// 4 constant) named, the body's accesses are global instead of flat ones
+// (which count as LDS and as memory accesses both) and its wave-uniform
+// twiddles scalar loads.
+template <int SPACE, class U>
+__device__ __forceinline__ U* uniform_ptr(U* p)
+{
+    const unsigned long long a = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    const unsigned long long u = ((unsigned long long)hi << 32) | lo;
+    return (U*)reinterpret_cast<__attribute__((address_space(SPACE))) U*>(u);
+}
+
 // One work item of a size-N grid; returns the workgroup's new unpublished
 // plane-item grid (or -1).  Kept out of line so that every size gets its own
 // register allocation instead of the maximum over all sizes.
 template <int N, int S, int T>
-__device__ __noinline__ int many_body(const float2* in, float2* out, const float2* __restrict__ tw, FusedCtl* ctl,
-                                      long offset, int grid, int slab, int idx, float2* lds, int tid, int pending)
+__device__ __noinline__ int many_body(const float2* in_, float2* out_, const float2* tw_, FusedCtl* ctl_,
+                                      long offset_, int grid_, int slab_, int idx_, float2* lds, int tid, int pending)
 {
+    const float2* in = uniform_ptr<1>(in_);
+    float2* out = uniform_ptr<1>(out_);
+    const float2* __restrict__ tw = uniform_ptr<4>(tw_);
+    FusedCtl* ctl = uniform_ptr<1>(ctl_);
+    const long offset = (long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(offset_ >> 32)) << 32) |
+                               (unsigned)__builtin_amdgcn_readfirstlane((int)offset_));
+    const int grid = __builtin_amdgcn_readfirstlane(grid_), slab = __builtin_amdgcn_readfirstlane(slab_),
+              idx = __builtin_amdgcn_readfirstlane(idx_);
     constexpr unsigned PER = many_per<N, T>();    // planes/slabs per item
     constexpr int TH = T / PER;                     // threads per plane/slab
     constexpr int RS = PlaneGeom<N>::RS;
