@@ -275,13 +275,14 @@ int fft3d_stream_copy(const void *src, void *dst, size_t bytes, fft3d_stream_t s
  * Heterogeneous batches in one launch.  `count` groups (1 <= count <= 16);
  * group g holds batch[g] cubic grids of nx[g] = ny[g] = nz[g] points per
  * side (sizes 24, 30, 32, 36, 40, 48, 50, 60, 64, 72, 80, 90, 96, 100, 120,
- * 128; FP32).  fft3d_exec_many transforms every grid of every group with ONE
- * persistent kernel launch: workgroups claim work items (xy-planes, then
- * xz-slabs of each grid) from a queue, and a grid's z work waits on a
- * per-grid counter of its finished planes.  A plan can instead run in the
- * grouped mode (two plain launches per group, the dense kernels) or a hybrid
- * of the two (see fft3d_plan_set_schedule), which the tuner picks when they
- * measure faster (few, large groups).  `in` and `out` are HOST arrays of
+ * 128; FP32).  fft3d_exec_many transforms every grid of every group in the
+ * call, in one of three modes: ONE persistent kernel launch, in which
+ * workgroups claim work items (xy-planes, then xz-slabs of each grid) from a
+ * queue and a grid's z work waits on a per-grid counter of its finished
+ * planes; the grouped mode (two plain launches per group, the dense kernels);
+ * or a hybrid of the two (see fft3d_plan_set_schedule).  An untuned plan
+ * takes the mode that its groups' bytes and launches make the cheapest
+ * estimate; the tuner measures them.  `in` and `out` are HOST arrays of
  * `count` device pointers, group g's buffer holding batch[g] grids in the
  * layout of fft3d_exec (in[g] == out[g] allowed).  The launch is
  * graph-capturable; a plan must not run concurrently with itself or with
@@ -292,7 +293,7 @@ int fft3d_stream_copy(const void *src, void *dst, size_t bytes, fft3d_stream_t s
  * per queue claim, and per group the radix order and z-tile width of its
  * plain passes) is taken from the tuning cache ($FFT3D_TUNE_CACHE, default
  * ~/.cache/fft3d/tune.json), else tuned at plan time when FFT3D_TUNE=1,
- * else a default.  The results are valid only while fft3d_plan_check
+ * else estimated.  The results are valid only while fft3d_plan_check
  * reports no expired wait (see there).
  */
 fft3d_plan_t fft3d_plan_many(int count, const int *nx, const int *ny, const int *nz, const int *batch,

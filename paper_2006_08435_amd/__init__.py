@@ -172,8 +172,7 @@ class Plan:
 
 
 class PlanMany:
-    """Heterogeneous batch: groups of cubic grids transformed by one
-    persistent launch.  ``groups`` is a list of (n, batch) pairs."""
+    """Heterogeneous batch: groups of cubic grids transformed in one call.  ``groups`` is a list of (n, batch) pairs."""
 
     def __init__(self, groups, direction: int = FFT3D_FORWARD, precision="fp32"):
         import ctypes

@@ -86,8 +86,9 @@ size_t plan_lds(const ManyPlan& mp, int threads, const bool* skip = nullptr)
 // mode with |threads| threads for the persistent part: a group whose plane
 // pass alone fills every compute unit (batch * n planes >= the plane
 // kernel's resident workgroups) runs its two plain passes, the others share
-// one persistent launch.
-int apply_schedule(fft3d_plan_s* p, int threads, int chunk)
+// one persistent launch.  plain (if given, with threads < 0): the groups that
+// run their plain passes instead of those.
+int apply_schedule(fft3d_plan_s* p, int threads, int chunk, const bool* plain = nullptr)
 {
     ManyPlan& mp = p->mp;
     if (threads == 0) {
@@ -102,7 +103,8 @@ int apply_schedule(fft3d_plan_s* p, int threads, int chunk)
     bool big[kMaxGroups] = {};
     if (hybrid)
         for (int g = 0; g < mp.ngroups; ++g)
-            big[g] = (long)mp.batch[g] * mp.n[g] >= (long)plane_pf_blocks_per_cu(mp.n[g]) * cus;
+            big[g] = plain ? plain[g]
+                           : (long)mp.batch[g] * mp.n[g] >= (long)plane_pf_blocks_per_cu(mp.n[g]) * cus;
     const bool* skip = hybrid ? big : nullptr;
     const size_t lds = plan_lds(mp, t, skip);
     long nitems = 0;
@@ -131,6 +133,39 @@ int apply_schedule(fft3d_plan_s* p, int threads, int chunk)
     mp.hybrid = hybrid;
     for (int g = 0; g < kMaxGroups; ++g) mp.big[g] = big[g];
     return FFT3D_OK;
+}
+
+// The default schedule of an untuned plan.  A group's two plain launches take
+// about kPlainUs each while it is small and the time of its bytes beyond; the
+// persistent launch costs kManyUs, and each of its groups the time of its
+// bytes.  The cheapest of three splits is taken: every group plain, the groups
+// that gain by it in one persistent launch, every group there.  Measured (us;
+// persistent launch of everything / plain launches / this rule):
+//   64^3 x 256 + 48 + 72 + 96 + 100 + 120        420 / 399 / 385 (the five single grids together)
+//   100 x 5 + 128 + 72 + 80 x 11 + 96 x 3 + 120 x 5   240 / 187 / plain
+//   36 x 240 + 50 x 145 + 100 x 7              353 / 207 / plain
+//   24 x 25 + 50                                28 /  19 / plain
+//   60 + 40 x 3 + 24 x 5 + 128 x 2 + 90 + 36 x 10      59 /  74 / everything
+constexpr double kPlainUs = 6.3, kManyUs = 33.0;
+constexpr double kPlainBytesPerUs = 6.0e6, kManyBytesPerUs = 5.5e6;
+
+int apply_default_schedule(fft3d_plan_s* p)
+{
+    ManyPlan& mp = p->mp;
+    bool plain[kMaxGroups] = {};
+    double grouped = 0.0, mixed = kManyUs, all = kManyUs;
+    for (int g = 0; g < mp.ngroups; ++g) {
+        const double bytes = 32.0 * mp.batch[g] * mp.n[g] * mp.n[g] * mp.n[g];   // two sweeps in and out
+        const double a = std::max(2.0 * kPlainUs, bytes / kPlainBytesPerUs), b = bytes / kManyBytesPerUs;
+        plain[g] = a <= b;
+        grouped += a;
+        all += b;
+        mixed += std::min(a, b);
+    }
+    // one launch overlaps what two parts run one after the other: it wins near-ties
+    if (all <= 1.05 * mixed && all < grouped) return apply_schedule(p, 1024, 1);
+    if (mixed < grouped) return apply_schedule(p, -1024, 1, plain);
+    return apply_schedule(p, 0, 1);
 }
 
 // Grouped mode: for each group its plane pass and its z pass, as a dense
@@ -515,10 +550,10 @@ fft3d_plan_t fft3d_plan_many(int count, const int* nx, const int* ny, const int*
         set_error(FFT3D_E_ALLOC);
         return nullptr;
     }
-    int threads = 1024, chunk = 1;
+    int threads = 0, chunk = 1;
     for (int g = 0; g < count; ++g) mp.zlines[g] = kAxisLines;
     const bool cached = cache_lookup(cache_key(p), count, threads, chunk, mp.kind, mp.zlines);
-    int rc = apply_schedule(p, threads, chunk);
+    int rc = cached ? apply_schedule(p, threads, chunk) : apply_default_schedule(p);
     if (rc == FFT3D_OK && !cached && env_flag("FFT3D_TUNE")) rc = tune(p);
     if (rc != FFT3D_OK) {
         free_plan(p);

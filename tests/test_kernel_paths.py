@@ -119,3 +119,19 @@ def test_energy_with_half_gradient(F, n, nz, b, direction):
     assert lib.fft3d_energy_vpsi_fwd(plan.handle, ct.data_ptr() + 8, Vt.data_ptr(), half.data_ptr(), E.data_ptr(),
                                      s) == -6
     assert lib.fft3d_energy_vpsi_bwd(plan.handle, half.data_ptr(), None, grad.data_ptr(), s) == -1
+
+
+@pytest.mark.parametrize("groups,mode", [
+    ([(24, 1), (50, 1)], "mode=grouped"),                                              # too little for one launch
+    ([(24, 2), (30, 1), (32, 1), (40, 1), (48, 1), (60, 1)], "mode=persistent"),       # six small groups
+    ([(64, 200), (24, 1), (30, 1), (36, 1), (48, 1), (50, 1)], "mode=hybrid grouped=64^3x200 "),
+])
+def test_default_schedule_of_a_mixed_batch(F, groups, mode):
+    plan = F.PlanMany(groups, FORWARD)
+    assert mode in plan.describe() and "default" in plan.describe()
+    xs = [workloads.uniform_grid(n, 800 + n, batch=b) for n, b in groups]
+    outs = plan.exec([torch.from_numpy(x).cuda() for x in xs])
+    for (n, b), x, y in zip(groups, xs, outs):
+        for j in {0, b - 1}:
+            assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), FORWARD)) <= TOL
+    assert F._lib.lib().fft3d_plan_check(plan.handle) == 0
