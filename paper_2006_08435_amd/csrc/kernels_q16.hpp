@@ -853,6 +853,48 @@ __global__ void __launch_bounds__(256) k_q16_quantize(const float2* in, long row
     if (lane == 0) ex[r] = (signed char)e;
 }
 
+// Rows of an even number of points: a lane converts pairs, one 8-byte load and
+// one 16-byte store each, four pairs in flight.  A workgroup takes `rpb` whole
+// rows (Q = C / 2 pairs each), so a pair's row is a 32-bit quotient: magic =
+// ceil(2^32 / Q) is exact for the pairs of a workgroup (rpb * Q <= 2048, or
+// one row).  Bound by HBM, 12 bytes a point.  67.1 million points: 196 us
+// with one point and a 64-bit division a thread, 159 with four points a lane
+// (its two stores each cover half of every cache line), 116 so.
+template <int FMT>
+__global__ void __launch_bounds__(256) k_q16_dequantize2(const uint2* __restrict__ pay, const signed char* __restrict__ ex,
+                                                         long rows, int Q, int rpb, unsigned magic,
+                                                         float2* __restrict__ out)
+{
+    constexpr int U = 4;
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    const long r0 = (long)blockIdx.x * rpb;
+    const int nr = (int)(rows - r0 < rpb ? rows - r0 : rpb), n = nr * Q;
+    const uint2* src = pay + r0 * Q;
+    f4v* dst = reinterpret_cast<f4v*>(out) + r0 * Q;
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * 256) {
+        uint2 u[U];
+        int e[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int i = i0 + k * 256;
+            if (i < n) {
+                u[k] = src[i];
+                e[k] = ex[r0 + (rpb == 1 ? 0 : (int)__umulhi((unsigned)i, magic))];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int i = i0 + k * 256;
+            if (i < n) {
+                const f4v v = {ldexpf(dec16<FMT>(u[k].x & 0xFFFFu), e[k]), ldexpf(dec16<FMT>(u[k].x >> 16), e[k]),
+                               ldexpf(dec16<FMT>(u[k].y & 0xFFFFu), e[k]), ldexpf(dec16<FMT>(u[k].y >> 16), e[k])};
+                __builtin_nontemporal_store(v, dst + i);
+            }
+        }
+    }
+}
+
+// Any row length: one point a thread.
 template <int FMT>
 __global__ void __launch_bounds__(256) k_q16_dequantize(const unsigned* pay, const signed char* ex, long rows, int C,
                                                         float2* out)

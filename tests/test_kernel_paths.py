@@ -135,3 +135,20 @@ def test_default_schedule_of_a_mixed_batch(F, groups, mode):
         for j in {0, b - 1}:
             assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), FORWARD)) <= TOL
     assert F._lib.lib().fft3d_plan_check(plan.handle) == 0
+
+
+@pytest.mark.parametrize("rows,C", [(1, 1), (7, 2), (5, 3), (4097, 4), (3, 6), (69, 30), (17, 128), (1025, 16), (2, 4096),
+                                    (3, 5002), (1, 4099)])
+@pytest.mark.parametrize("precision", ["fp16", "bf16"])
+def test_dequantize_rows(F, rows, C, precision):
+    """Every value is payload * 2^exponent, bit for bit: pairs and single
+    points, ragged last workgroups, rows longer than a workgroup's share."""
+    rng = np.random.default_rng(900 + rows + C)
+    x = workloads.uniform_grid((C, rows, 1), 900 + rows + C)[0] * np.exp2(rng.integers(-40, 40, (rows, 1)))
+    buf = F.quantize(torch.from_numpy(x.astype(np.complex64)).cuda(), precision)
+    got = F.dequantize(buf, (rows, C), precision).cpu().numpy()
+    raw = buf.cpu()
+    pay = raw[:4 * rows * C].view(torch.float16 if precision == "fp16" else torch.bfloat16).double().numpy()
+    exp = raw[4 * rows * C:].numpy().view(np.int8).astype(np.float64)
+    want = pay.reshape(rows, C, 2) * np.exp2(exp)[:, None, None]
+    assert np.array_equal(got.view(np.float32).reshape(rows, C, 2).astype(np.float64), want)
