@@ -117,17 +117,38 @@ HlocFn axis_hloc_fn(int n)
 
 constexpr int kDensityLines = 32;
 
+// Orbital ranges of the density's z pass, from sweeps of both limits below.
+// Fewer tiles than compute units need more workgroups at any price (ranges of
+// four orbitals or more: 30 orbitals at 64^3 47 -> 29 us, 256 at 32^3 250 ->
+// 31).  From 200 tiles on (80^2 lines) the split only evens out the last turn
+// and hides latency, and the partial sums cost: ranges of 16 orbitals or more
+// (128 at 96^3 342 -> 252 us; 40 at 90^3 143 -> 139, with ranges of ten 151).
+// 512 tiles (128^2 lines) are two for every compute unit and gain nothing (32
+// orbitals at 128^3 147 us in one range, 157 in two).
+static int density_splits(long tiles, int batch)
+{
+    if (tiles >= 512) return 1;
+    const long want = (tiles >= 200 ? 1536 : 1024) / tiles, most = batch / (tiles >= 200 ? 16 : 4);
+    const long s = want < most ? want : most;
+    return (int)(s < 1 ? 1 : s);
+}
+
 template <int N>
-static hipError_t launch_density(const float2* buf, const float2* tw, const AxisMap& m, int batch, long vol,
+static hipError_t launch_density(float2* buf, const float2* tw, const AxisMap& m, int batch, long vol,
                                  const float* occ, float* rho, double R2, int mode, hipStream_t st)
 {
-    const long blocks = (m.lines + kDensityLines - 1) / kDensityLines;
+    const int tiles = (int)((m.lines + kDensityLines - 1) / kDensityLines), splits = density_splits(tiles, batch);
+    const OrbitalRanges ranges{splits, batch / splits, batch % splits};
+    const dim3 grid((unsigned)tiles, (unsigned)splits), block(AxisGeom<N, kDensityLines>::T);
     if (mode)
-        hipLaunchKernelGGL((k_axis_density<N, kDensityLines, 1>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kDensityLines>::T), 0, st, buf, tw, m, batch, vol, occ, rho, R2);
+        hipLaunchKernelGGL((k_axis_density<N, kDensityLines, 1>), grid, block, 0, st, buf, tw, m, vol, occ, rho, R2,
+                           ranges);
     else
-        hipLaunchKernelGGL((k_axis_density<N, kDensityLines, 0>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kDensityLines>::T), 0, st, buf, tw, m, batch, vol, occ, rho, R2);
+        hipLaunchKernelGGL((k_axis_density<N, kDensityLines, 0>), grid, block, 0, st, buf, tw, m, vol, occ, rho, R2,
+                           ranges);
+    if (splits > 1)
+        hipLaunchKernelGGL((k_density_sum<kDensityLines>), dim3((unsigned)((vol + 255) / 256)), dim3(256), 0, st, buf,
+                           rho, vol, (int)m.lines, ranges);
     return hipGetLastError();
 }
 

@@ -1436,19 +1436,35 @@ k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __rest
     }
 }
 
+// Ranges of consecutive orbitals: `count` ranges of `per` each, the first
+// `extra` of them one longer.
+struct OrbitalRanges {
+    int count, per, extra;
+    __device__ __forceinline__ int first(int k) const { return k * per + (k < extra ? k : extra); }
+};
+
 // Density epilogue of the inverse transform: rho(r) = sum_b occ[b]
 // |psi_b(r)|^2, psi_b the inverse z-transform of orbital b of `buf` (already
 // transformed along x and y; orbitals `vol` apart).  Each workgroup owns L
 // adjacent z-lines of the grid (map: the lines of ONE grid) and loops over
 // the orbitals: stage 0 from HBM into LDS, the other stages in LDS, then each
 // thread adds occ[b] |psi|^2 at its fixed points in registers (FP32 FMA, in
-// fixed orbital order, last first: deterministic).  psi is never stored; rho ([z][y][x] real)
-// is written once.  MODE 1 (cutoff R2): loads only of the planes with
-// Gz^2 < R2 (the others were not written by the pruned plane pass).
+// fixed orbital order, last first: deterministic).  psi is never stored.  MODE 1
+// (cutoff R2): loads only of the planes with Gz^2 < R2 (the others were not
+// written by the pruned plane pass).
+// The lines of one grid fill the device only once or twice over (288 tiles of
+// 32 lines at 96^2, four waves each), and a workgroup alone on its compute unit
+// waits for every barrier and load, so the orbitals are split into
+// ranges of consecutive ones, each with its own workgroups.  With one range
+// rho ([z][y][x] real) is written here.  Otherwise a workgroup leaves its
+// partial sums where it alone has read, in the first half of the runs of its
+// lines in its first orbital (float `line` of the run of element e), and
+// k_density_sum adds the ranges.  128 orbitals at 96^3 with a cutoff: the
+// density 346 us with one range, 252 with five.
 template <int N, int L, int MODE>
 __global__ void __launch_bounds__((AxisGeom<N, L>::T))
-k_axis_density(const float2* buf, const float2* __restrict__ tw, AxisMap m, int batch, long vol,
-               const float* __restrict__ occ, float* __restrict__ rho, double R2)
+k_axis_density(float2* buf, const float2* __restrict__ tw, AxisMap m, long vol,
+               const float* __restrict__ occ, float* __restrict__ rho, double R2, OrbitalRanges ranges)
 {
     using G = AxisGeom<N, L>;
     using P = Plan1D<N>;
@@ -1468,17 +1484,14 @@ k_axis_density(const float2* buf, const float2* __restrict__ tw, AxisMap m, int 
         for (int i = tid; i < P::tw_len; i += T) tw_lds[i] = tw[i];
         tw = tw_lds;
     }
-    const long tile = rev_tile();
-    const long l0 = tile * L;
+    const int range = gridDim.y - 1 - blockIdx.y;   // the last one first: its orbitals were written last
+    const int b0 = ranges.first(range), b1 = ranges.first(range + 1);
+    const long l0 = rev_tile() * L;
     const int myline = tid % L;
     const long li = l0 + myline;
     const int valid = (int)((m.lines - l0) < L ? (m.lines - l0) : L);
-    long gbase = 0;
-    if (li < m.lines) {
-        const long o = li / m.nx;
-        const long x = li - o * m.nx;
-        gbase = (o / m.odiv) * m.shi + (o % m.odiv) * m.slo + x;
-    }
+    // the lines of one grid are its (y, x) points: line li starts at point li
+    const long gbase = li < m.lines ? li : 0;
     float2 pre[IT0][R0];
     auto load0 = [&](int b) {
         const float2* src = buf + (long)b * vol + gbase;
@@ -1505,8 +1518,8 @@ k_axis_density(const float2* buf, const float2* __restrict__ tw, AxisMap m, int 
     const LdsAcc<1, G::LP> a{lds};
     // orbitals from the last to the first: the plane pass before this one
     // wrote the last orbitals last, so they are the ones still in the caches
-    if (batch > 0) load0(batch - 1);
-    for (int b = batch - 1; b >= 0; --b) {
+    load0(b1 - 1);
+    for (int b = b1 - 1; b >= b0; --b) {
 #pragma unroll
         for (int it = 0; it < IT0; ++it) {
             const int bb = tid + it * T, j = bb / L;
@@ -1517,7 +1530,7 @@ k_axis_density(const float2* buf, const float2* __restrict__ tw, AxisMap m, int 
             }
         }
         __syncthreads();
-        if (b > 0) load0(b - 1);
+        if (b > b0) load0(b - 1);
         if constexpr (P::stages > 1) {
             run_tail<N, 1, L, T, 1, false>(a, a, tw, tid, valid);
             __syncthreads();
@@ -1537,9 +1550,30 @@ k_axis_density(const float2* buf, const float2* __restrict__ tw, AxisMap m, int 
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * T;
-            if ((N * L) % T == 0 || i < N * L) rho[gbase + (long)(i / L) * m.es] = acc[k];
+            if ((N * L) % T == 0 || i < N * L) {
+                const long e = (long)(i / L) * m.es;
+                if (ranges.count == 1) rho[gbase + e] = acc[k];
+                else reinterpret_cast<float*>(buf + (long)b0 * vol + l0 + e)[myline] = acc[k];
+            }
         }
     }
+}
+
+// rho = the sum of the ranges' partial sums that k_axis_density left in buf,
+// in a fixed order: one thread a point, lanes along the lines.
+template <int L>
+__global__ void __launch_bounds__(256)
+k_density_sum(const float2* __restrict__ buf, float* __restrict__ rho, long vol, int lines, OrbitalRanges ranges)
+{
+    const long r = (long)blockIdx.x * 256 + threadIdx.x;
+    if (r >= vol) return;
+    const int off = (int)(r % lines) % L;
+    const float2* run = buf + (r - off);
+    float s = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < ranges.count; ++k)
+        s += reinterpret_cast<const float*>(run + (long)ranges.first(k) * vol)[off];
+    rho[r] = s;
 }
 
 template <int N, int L>

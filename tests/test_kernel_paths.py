@@ -152,3 +152,29 @@ def test_dequantize_rows(F, rows, C, precision):
     exp = raw[4 * rows * C:].numpy().view(np.int8).astype(np.float64)
     want = pay.reshape(rows, C, 2) * np.exp2(exp)[:, None, None]
     assert np.array_equal(got.view(np.float32).reshape(rows, C, 2).astype(np.float64), want)
+
+
+@pytest.mark.parametrize("n,nz,b", [(5, 6, 3), (5, 6, 4), (5, 6, 9), (30, 12, 41), (75, 8, 33), (80, 4, 31), (80, 4, 32),
+                                    (90, 3, 50), (128, 2, 40)])
+@pytest.mark.parametrize("cut", [False, True])
+def test_density_ranges(F, n, nz, b, cut):
+    """One orbital range and several, uneven ranges, a ragged last tile of
+    lines, work on top of c."""
+    r2 = (min(n, nz) / 2.5) ** 2
+    gz = workloads.signed_freq(nz)[:, None, None]
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + gz ** 2) < r2
+    c = workloads.uniform_grid((n, n, nz), 1000 + n, batch=b)
+    if cut:
+        c = (c * inside).astype(np.complex64)
+    occ = np.random.default_rng(b).uniform(0, 2, b).astype(np.float32)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    if cut:
+        plan.set_cutoff(r2)
+    ct, ot = torch.from_numpy(c).cuda(), torch.from_numpy(occ).cuda()
+    rho = plan.density(ct, ot)
+    again = plan.density(ct, ot, work=ct)
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    want = np.tensordot(occ.astype(np.float64), np.abs(psi) ** 2, axes=1)
+    assert rel(rho.cpu().numpy(), want) <= TOL
+    assert torch.equal(rho, again)
