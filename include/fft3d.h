@@ -176,10 +176,12 @@ int fft3d_plan_describe(fft3d_plan_t plan, char *buf, size_t len);
  *     only those lines and stores only the points inside the sphere, which
  *     hold the dense transform's values; all other output points are left
  *     unspecified (they may hold intermediate values).
- *   Both use the dense schedule's butterflies in the dense order; the
+ *   Both use the two-pass dense schedule's butterflies in its order; the
  *   compiler may contract a few multiply-adds of the pruned kernels into
- *   FMAs differently, so results agree with the dense plan's to FP32
- *   rounding (in practice the inverse reproduces them bit for bit).
+ *   FMAs differently, and batches of cubic grids of up to 32 points a side have
+ *   a dense form of their own, so results agree with the dense plan's to FP32
+ *   rounding (in practice the inverse reproduces the two-pass form and single
+ *   small cubes bit for bit).
  * Applies to fft3d_exec and fft3d_exec_pass (the pass list keeps its two
  * passes, plane then z, with pruned kernels); the energy entry points are
  * not affected.

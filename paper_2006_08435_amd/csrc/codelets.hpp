@@ -1,5 +1,5 @@
 // Register-resident R-point DFT butterflies (R = 1, 2, 3, 4, 5, 6, 8, 9, 10,
-// 12, 15, 16) on
+// 12, 15, 16, and whole lines of 18, 20, 24, 25, 27, 30 and 32 points) on
 // float2 complex values, for exponent sign S (-1 forward, +1 inverse):
 //   X[k] = sum_n x[n] exp(S * 2 pi i n k / R),  in place on v[0..R).
 // Constants are written to float precision from their closed forms.
@@ -206,6 +206,85 @@ template <int S> __device__ __forceinline__ void dft9(float2* v)
     }
 }
 
+// cos and sin of 2 pi m / n in double precision at compile time: the angle is
+// folded by whole numbers into [0, pi / 4], where a few Taylor terms suffice.
+struct CosSin {
+    double c, s;
+};
+constexpr CosSin unit_root(int m, int n)
+{
+    m %= n;
+    if (8 * m > 4 * n) {   // above pi: mirror
+        const CosSin r = unit_root(n - m, n);
+        return CosSin{r.c, -r.s};
+    }
+    if (8 * m > 2 * n) {   // above pi / 2: 2 pi m / n = pi - 2 pi (n - 2 m) / (2 n)
+        const CosSin r = unit_root(n - 2 * m, 2 * n);
+        return CosSin{-r.c, r.s};
+    }
+    if (8 * m > n) {       // above pi / 4: 2 pi m / n = pi / 2 - 2 pi (n - 4 m) / (4 n)
+        const CosSin r = unit_root(n - 4 * m, 4 * n);
+        return CosSin{r.s, r.c};
+    }
+    const double a = 6.283185307179586476925 * m / n, a2 = a * a;
+    double c = 1.0, s = 1.0, tc = 1.0, ts = 1.0;
+    for (int k = 1; k <= 9; ++k) {
+        tc *= -a2 / ((2 * k - 1) * (2 * k));
+        ts *= -a2 / ((2 * k) * (2 * k + 1));
+        c += tc;
+        s += ts;
+    }
+    return CosSin{c, a * s};
+}
+
+// a * exp(S * 2 pi i M / N), M and N compile-time constants
+template <int M, int N, int S> __device__ __forceinline__ float2 mul_root(float2 a)
+{
+    if constexpr (M % N == 0) {
+        return a;
+    } else if constexpr (8 * M == N) {
+        return mul_w8<S>(a);
+    } else if constexpr (4 * M == N) {
+        return mul_si<S>(a);
+    } else if constexpr (8 * M == 3 * N) {
+        return mul_w8_3<S>(a);
+    } else {
+        constexpr CosSin w = unit_root(M, N);
+        return mul_cs<S>(a, (float)w.c, (float)w.s);
+    }
+}
+
+// R1 R2 points by Cooley and Tukey: n = R2 n1 + n2, k = k1 + R1 k2, twiddles
+// W_R^(n2 k1) between the two layers.
+template <int R1, int R2, int S, int I = 0> __device__ __forceinline__ void ct_twiddles(float2 (*a)[R1])
+{
+    if constexpr (I < R1 * R2) {
+        constexpr int n2 = I / R1, k1 = I % R1;
+        a[n2][k1] = mul_root<n2 * k1, R1 * R2, S>(a[n2][k1]);
+        ct_twiddles<R1, R2, S, I + 1>(a);
+    }
+}
+template <int R1, int R2, int S> __device__ __forceinline__ void dft_ct(float2* v)
+{
+    float2 a[R2][R1];
+#pragma unroll
+    for (int n2 = 0; n2 < R2; ++n2) {
+#pragma unroll
+        for (int n1 = 0; n1 < R1; ++n1) a[n2][n1] = v[R2 * n1 + n2];
+        dft<R1, S>(a[n2]);
+    }
+    ct_twiddles<R1, R2, S>(a);
+#pragma unroll
+    for (int k1 = 0; k1 < R1; ++k1) {
+        float2 b[R2];
+#pragma unroll
+        for (int n2 = 0; n2 < R2; ++n2) b[n2] = a[n2][k1];
+        dft<R2, S>(b);
+#pragma unroll
+        for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = b[k2];
+    }
+}
+
 template <int R, int S> __device__ __forceinline__ void dft(float2* v)
 {
     if constexpr (R == 1) {
@@ -231,6 +310,20 @@ template <int R, int S> __device__ __forceinline__ void dft(float2* v)
         dft_pfa<3, 5, S>(v);
     } else if constexpr (R == 16) {
         dft16<S>(v);
+    } else if constexpr (R == 18) {
+        dft_pfa<2, 9, S>(v);
+    } else if constexpr (R == 20) {
+        dft_pfa<4, 5, S>(v);
+    } else if constexpr (R == 24) {
+        dft_pfa<8, 3, S>(v);
+    } else if constexpr (R == 25) {
+        dft_ct<5, 5, S>(v);
+    } else if constexpr (R == 27) {
+        dft_ct<3, 9, S>(v);
+    } else if constexpr (R == 30) {
+        dft_pfa<6, 5, S>(v);
+    } else if constexpr (R == 32) {
+        dft_ct<4, 8, S>(v);
     } else {
         static_assert(R == 16, "unsupported radix");
     }

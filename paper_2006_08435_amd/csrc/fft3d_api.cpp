@@ -20,10 +20,11 @@ thread_local int g_last_error = FFT3D_OK;
 }  // namespace
 
 enum Scheme {
-    kCube = 0,    // whole grid per workgroup
+    kCube = 0,    // whole grid per workgroup, radix stages in LDS (cubic, up to 16)
     kPlaneZ = 1,  // xy-plane pass + strided z pass (Nx == Ny)
     kAxes = 2,    // x rows, strided y, strided z
     kFused = 3,   // persistent plane + z-slab kernel (cubic)
+    kCubeLines = 5, // whole grid per workgroup, a line a thread (cubic, 8 to 32)
     kQ16 = 4,     // scaled 16-bit storage, radix-16 on the matrix cores (cubic, 16 | N)
 };
 
@@ -74,6 +75,16 @@ static int fused_mode()
 {
     const char* e = std::getenv("FFT3D_FUSED");
     return e ? std::atoi(e) : 0;
+}
+
+static int device_cus(int dev)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        cus = 1;
+    }
+    return cus;
 }
 
 int last_error_value() { return g_last_error; }
@@ -148,8 +159,10 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
         p->q16_valu = !env_flag("FFT3D_Q16_MFMA");
     }
     else if (large) p->scheme = kAxes;
-    else if (nx == ny && ny == nz && nx <= kCubeMaxN) p->scheme = kCube;
     else if (nx == ny && ny == nz && fused_fn(nx, direction) && fused_mode() > 0) p->scheme = kFused;
+    else if (nx == ny && ny == nz && cube_lines_fn(nx, direction) && cube_lines_ok(nx, batch, device_cus(dev)))
+        p->scheme = kCubeLines;
+    else if (nx == ny && ny == nz && cube_fn(nx, direction)) p->scheme = kCube;
     else if (nx == ny) p->scheme = kPlaneZ;
     else p->scheme = kAxes;
 
@@ -252,8 +265,8 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
             p->fused_lag = lg && std::atoi(lg) > 0 ? std::atoi(lg) : (2 * (res_x / nxcc) + nx - 1) / nx + 2;
         }
         p->passes.push_back({Pass::kFusedK, nx, B, {}, p->tw_x});
-    } else if (p->scheme == kCube) {
-        p->passes.push_back({Pass::kCubeK, nx, B, {}, p->tw_x});
+    } else if (p->scheme == kCube || p->scheme == kCubeLines) {
+        p->passes.push_back({p->scheme == kCube ? Pass::kCubeK : Pass::kCubeLinesK, nx, B, {}, p->tw_x});
     } else if (p->scheme == kPlaneZ) {
         if (plane_pf_fn(nx, direction) && !env_flag("FFT3D_NO_PLANE_PF")) {
             int cus = 0;
@@ -395,6 +408,7 @@ static hipError_t run_pass(const fft3d_plan_s* p, const Pass& ps, const float2* 
     const float2* tw = p->d_tw + ps.tw;
     switch (ps.kind) {
     case Pass::kCubeK: return cube_fn(ps.n, S)(src, dst, tw, ps.count, st);
+    case Pass::kCubeLinesK: return cube_lines_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kPlaneK: return plane_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kPlanePfK:
         return plane_pf_fn(ps.n, S)(src, dst, tw, ps.count, ps.grid, 0, nullptr, nullptr, 1, true, st);
@@ -1000,6 +1014,10 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
         snprintf(tmp, sizeof tmp, "cube n=%d radices=%s threads=%d lds=%d grids=%d", p->nx,
                  radices(p->nx).c_str(), k.threads, k.lds_bytes, p->batch);
         d = tmp;
+    } else if (p->scheme == kCubeLines) {
+        const KernelInfo k = cube_lines_info(p->nx);
+        snprintf(tmp, sizeof tmp, "cube lines n=%d threads=%d lds=%d grids=%d", p->nx, k.threads, k.lds_bytes, p->batch);
+        d = tmp;
     } else if (p->scheme == kPlaneZ) {
         const KernelInfo a = plane_info(p->nx), b = axis_str_info(p->nz);
         snprintf(tmp, sizeof tmp, "plane n=%d radices=%s threads=%d lds=%d planes=%ld; z n=%d radices=%s threads=%d lds=%d",
@@ -1022,7 +1040,7 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
     for (size_t i = 0; i < p->passes.size(); ++i) {
         static const char* names[] = {"k_cube",      "k_plane",    "k_plane_pf",     "k_axis_row",
                                       "k_axis_str",  "k_fused",    "k_q16_plane",    "k_q16_slab",
-                                      "k_plane_pruned", "k_axis_str_pruned"};
+                                      "k_plane_pruned", "k_axis_str_pruned", "k_plane_real", "k_cube_lines"};
         d += (i ? "," : "") + std::string(names[p->passes[i].kind]);
     }
     if (buf && len) {

@@ -2,8 +2,10 @@
 // and exponent sign.  Layout of every grid: [batch][z][y][x], x contiguous,
 // interleaved complex64.
 //
-//   k_cube<N,S>      one whole N^3 grid per workgroup, all three 1D passes in
-//                    LDS (grids small enough to live on one compute unit).
+//   k_cube<N,S>      one whole N^3 grid per workgroup (N <= 16), all three 1D
+//                    passes in LDS.
+//   k_cube_lines<N,S> one whole N^3 grid per workgroup (N <= 32), a line a
+//                    thread in registers, exchanged through LDS.
 //   k_plane<N,S>     pass A of the two-pass form: one xy-plane (Nx = Ny = N)
 //                    per workgroup; x transform, LDS transpose by access
 //                    pattern, y transform, store.
@@ -341,6 +343,94 @@ k_cube(const float2* in, float2* out, const float2* __restrict__ tw)
         __syncthreads();
     }
     lds_to_tile<N * N, N, G::YS, T>(lds, out + base, tid);
+}
+
+// Whole N^3 grid per workgroup with a line of N points in each thread's
+// registers: thread t transforms line t of the N^2 lines along z, then along
+// x, then along y, and LDS only carries the two exchanges between them.  The
+// z lines are read with lanes along x and y (whole planes at a time), the y
+// lines written with lanes along x.  SPLIT: the exchanges go part by part
+// (real, then imaginary), so that a grid of up to 32^3 (256 KB) passes
+// through 4 bytes a point of LDS.  One read and one write of the grid, where
+// the plane and z passes make two of each.  Measured against those, inverse +
+// forward in us: 1024 x 20^3 89 -> 44, 400 x 27^3 103 -> 49, 400 x 30^3 133 ->
+// 85, 4096 x 32^3 1658 -> 877 (644 at the copy rate); up to 16 points against
+// k_cube: 1024 x 16^3 26.4 -> 22.6.  At 30
+// and 32 points one workgroup fills a compute unit, and a batch of two turns of
+// the device pays for its ragged last turn.
+template <int N>
+struct CubeLines {
+    static constexpr int P = odd_stride(N);   // LDS pitch of a row of x, odd: reads along x do not conflict
+    static constexpr bool SPLIT = N > 16;
+    static constexpr int WORDS = N * N * P;
+    static constexpr int T = round_up(N * N, 64);
+    using W = typename std::conditional<SPLIT, float, float2>::type;
+    static_assert(T <= 1024, "one line a thread");
+};
+
+template <int N, int S>
+__global__ void __launch_bounds__(CubeLines<N>::T) k_cube_lines(const float2* in, float2* out)
+{
+    using G = CubeLines<N>;
+    constexpr int P = G::P;
+    __shared__ typename G::W lds[G::WORDS];
+    const int t = threadIdx.x;
+    const bool on = N * N % 64 == 0 || t < N * N;
+    const int hi = t / N, lo = t - hi * N;
+    const long base = (long)blockIdx.x * (N * N * N);
+    // element e of this thread's line in the tile [z][y][x] (rows of pitch P)
+    auto z_line = [&](int e) { return (e * N + hi) * P + lo; };   // line (y, x) = (hi, lo)
+    auto x_line = [&](int e) { return t * P + e; };               // line (z, y) = (hi, lo)
+    auto y_line = [&](int e) { return (hi * N + e) * P + lo; };   // line (z, x) = (hi, lo)
+    float2 v[N];
+    // every thread's line v from its place `from` in the tile to its place `to`
+    auto exchange = [&](auto from, auto to) {
+        if constexpr (G::SPLIT) {
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) lds[from(e)] = v[e].x;
+            }
+            __syncthreads();
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[e].x = lds[to(e)];
+            }
+            __syncthreads();
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) lds[from(e)] = v[e].y;
+            }
+            __syncthreads();
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[e].y = lds[to(e)];
+            }
+        } else {
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) lds[from(e)] = v[e];
+            }
+            __syncthreads();
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) v[e] = lds[to(e)];
+            }
+        }
+    };
+    if (on) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[e] = in[base + e * (N * N) + t];
+        dft<N, S>(v);
+    }
+    exchange(z_line, x_line);
+    if (on) dft<N, S>(v);
+    __syncthreads();   // the reads above are done before the tile is written again
+    exchange(x_line, y_line);
+    if (on) {
+        dft<N, S>(v);
+#pragma unroll
+        for (int e = 0; e < N; ++e) out[base + (hi * N + e) * N + lo] = v[e];
+    }
 }
 
 // ----------------------------------------------------------------- plane --

@@ -29,13 +29,33 @@ using AxisRowFn = hipError_t (*)(const float2* in, float2* out, const float2* tw
 using FusedFn = hipError_t (*)(const float2* in, float2* out, const float2* tw, FusedCtl* ctl, int batch, int lag,
                                int grid, int chunk, hipStream_t st);
 
-// Largest cubic length handled by the whole-grid-in-LDS kernel.
-constexpr int kCubeMaxN = 16;
 // Lines per workgroup of the strided-axis and row kernels.
 constexpr int kAxisLines = 64;
 constexpr int kRowLines = 16;
 
 CubeFn cube_fn(int n, int sign);
+// Whole grid per workgroup with a line a thread (nullptr: no such length); it
+// has its twiddles as constants.
+CubeFn cube_lines_fn(int n, int sign);
+// Whether it takes a batch of n^3 grids (8 <= n <= 32) on `cus` compute units.
+// Up to 16 points k_cube has the same butterflies as the passes that a cutoff
+// prunes and is as fast until the device is full several times over (512 /
+// 1024 grids of 16^3, inverse + forward, 17.0 -> 15.0 / 26.4 -> 22.6 us); 18
+// and 20 always (one 20^3 grid 19.2 -> 13.8 us); 24 from a few grids on (single
+// ones differ little).  Above, one workgroup's whole grid takes longer than its
+// planes spread over the device, until the batch fills a good part of it: 25^3
+// and 27^3 at 32 / 64 grids 0.91 / 1.15 times as fast as the passes, 30^3 at 64
+// / 96 grids 0.96 / 1.2 times, 32^3 at 64 / 96 0.92 / 1.02 times.  A 32^3 batch
+// just over one grid a compute unit pays for a second turn (264 grids 89 -> 91
+// us, 280 grids 94 -> 91).
+constexpr bool cube_lines_ok(int n, int batch, int cus)
+{
+    if (n <= 16) return batch >= 2 * cus;
+    if (n <= 20) return true;
+    if (n <= 24) return batch >= cus / 32;
+    if (n <= 27) return batch >= cus / 4;
+    return batch >= cus * 3 / 8 && (n < 32 || batch <= cus || batch > cus + cus / 16);
+}
 long axis_str_blocks(long lines);
 hipError_t launch_sum_partials(const double* partials, long n, double* out, hipStream_t st);
 PlaneFn plane_fn(int n, int sign);
@@ -131,6 +151,7 @@ struct KernelInfo {
     int lds_bytes;
 };
 KernelInfo cube_info(int n);
+KernelInfo cube_lines_info(int n);
 KernelInfo plane_info(int n);
 KernelInfo axis_str_info(int n);
 KernelInfo axis_row_info(int n);

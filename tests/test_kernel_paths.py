@@ -178,3 +178,23 @@ def test_density_ranges(F, n, nz, b, cut):
     want = np.tensordot(occ.astype(np.float64), np.abs(psi) ** 2, axes=1)
     assert rel(rho.cpu().numpy(), want) <= TOL
     assert torch.equal(rho, again)
+
+
+@pytest.mark.parametrize("n,b", [(8, 511), (8, 512), (9, 513), (15, 512), (16, 600), (18, 2), (20, 1), (24, 7), (24, 8), (25, 63), (25, 64),
+                                 (27, 64), (30, 95), (30, 96), (32, 95), (32, 97)])
+@pytest.mark.parametrize("sign", [INVERSE, FORWARD])
+def test_whole_grid_lines(F, n, b, sign):
+    """The whole-grid kernel at every kind of length (one line a thread, waves
+    with idle lanes) and on both sides of its batch limits; in place too."""
+    x = workloads.uniform_grid(n, 1100 + n, batch=b)
+    plan = F.Plan(n, n, n, b, "fp32", sign)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    least = 2 * cus if n <= 16 else 1 if n <= 20 else cus // 32 if n <= 24 else cus // 4 if n <= 27 else cus * 3 // 8
+    assert plan.describe().startswith("cube lines" if b >= least else "cube" if n <= 16 else "plane")
+    xt = torch.from_numpy(x).cuda()
+    y = plan.exec(xt)
+    z = xt.clone()
+    plan.exec(z, z)
+    assert torch.equal(y, z)
+    for j in {0, b // 2, b - 1}:
+        assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
