@@ -279,6 +279,10 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
             p->passes.push_back({Pass::kPlaneK, nx, B * nz, {}, p->tw_x});
         }
         if (nz > 1) p->passes.push_back({Pass::kStrK, nz, 0, zmap, p->tw_z});
+    } else if (rect_init(nx, ny, B * nz, direction)) {
+        // the plane in LDS, as one pass (nx != ny, or a larger nz)
+        p->passes.push_back({Pass::kRectK, nx, B * nz, {}, p->tw_x});
+        if (nz > 1) p->passes.push_back({Pass::kStrK, nz, 0, zmap, p->tw_z});
     } else {
         if (nx > 1) p->passes.push_back({Pass::kRowK, nx, B * nz * ny, {}, p->tw_x});
         if (ny > 1) p->passes.push_back({Pass::kStrK, ny, 0, ymap, p->tw_y});
@@ -409,6 +413,8 @@ static hipError_t run_pass(const fft3d_plan_s* p, const Pass& ps, const float2* 
     switch (ps.kind) {
     case Pass::kCubeK: return cube_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kCubeLinesK: return cube_lines_fn(ps.n, S)(src, dst, tw, ps.count, st);
+    case Pass::kRectK:
+        return launch_plane_rect(src, dst, p->d_tw + p->tw_x, p->d_tw + p->tw_y, p->nx, p->ny, ps.count, S, st);
     case Pass::kPlaneK: return plane_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kPlanePfK:
         return plane_pf_fn(ps.n, S)(src, dst, tw, ps.count, ps.grid, 0, nullptr, nullptr, 1, true, st);
@@ -1040,7 +1046,7 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
     for (size_t i = 0; i < p->passes.size(); ++i) {
         static const char* names[] = {"k_cube",      "k_plane",    "k_plane_pf",     "k_axis_row",
                                       "k_axis_str",  "k_fused",    "k_q16_plane",    "k_q16_slab",
-                                      "k_plane_pruned", "k_axis_str_pruned", "k_plane_real", "k_cube_lines"};
+                                      "k_plane_pruned", "k_axis_str_pruned", "k_plane_real", "k_cube_lines", "k_plane_rect"};
         d += (i ? "," : "") + std::string(names[p->passes[i].kind]);
     }
     if (buf && len) {

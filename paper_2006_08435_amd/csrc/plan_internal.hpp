@@ -28,7 +28,7 @@ int twiddles_into(float2* t, int cap, int n, int sign, int kind = 0);
 // every later pass works in place on the output buffer.
 struct Pass {
     enum Kind { kCubeK, kPlaneK, kPlanePfK, kRowK, kStrK, kFusedK, kQ16PlaneK, kQ16SlabK, kPlanePrunedK, kStrPrunedK, kRealK,
-                kCubeLinesK } kind;
+                kCubeLinesK, kRectK } kind;
     int n;        // transform length of this pass
     long count;   // grids / planes / rows (cube, plane, row kinds)
     AxisMap map;  // strided kind

@@ -123,6 +123,18 @@ using AxisVarFn = hipError_t (*)(const float2* in, float2* out, const float2* tw
 PlaneVarFn plane_variant_fn(int n, int sign, int kind);
 AxisVarFn axis_variant_fn(int n, int sign, int kind, int lines);
 
+// Plane pass of x and y lengths up to 128 (kernels_rect.hpp), for grids that
+// the square plane pass does not take.  rect_init, once a plan: whether it takes
+// this plane, with its kernel made ready.
+struct RectArgs;
+bool rect_init(int nx, int ny, long planes, int sign);
+hipError_t launch_plane_rect(const float2* in, float2* out, const float2* tw_x, const float2* tw_y, int nx, int ny,
+                             long planes, int sign, hipStream_t st);
+hipError_t rect_fwd(int cls, const RectArgs& a, unsigned grid, size_t lds, hipStream_t st);
+hipError_t rect_inv(int cls, const RectArgs& a, unsigned grid, size_t lds, hipStream_t st);
+const void* rect_fwd_kernel(int cls);
+const void* rect_inv_kernel(int cls);
+
 // Heterogeneous persistent kernel (kernels_many.hpp); threads is 512 or 1024.
 hipError_t launch_many(const ManyArgs& a, int sign, int threads, int grid, size_t lds_bytes, hipStream_t st);
 int many_blocks_per_cu(int threads, size_t lds_bytes);

@@ -198,3 +198,25 @@ def test_whole_grid_lines(F, n, b, sign):
     assert torch.equal(y, z)
     for j in {0, b // 2, b - 1}:
         assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
+
+
+@pytest.mark.parametrize("nx,ny,nz,b", [(15, 16, 2, 3), (8, 25, 3, 2), (100, 2, 1, 5), (2, 100, 3, 2), (32, 32, 135, 1),
+                                        (9, 128, 2, 2), (128, 8, 2, 2), (64, 60, 2, 3), (81, 50, 3, 2), (64, 81, 2, 1),
+                                        (100, 72, 2, 2), (75, 125, 2, 1), (128, 80, 2, 2), (128, 81, 1, 2),
+                                        (120, 125, 2, 1), (128, 125, 3, 1), (128, 128, 144, 1), (12, 16, 5, 2), (12, 20, 8, 256), (12, 20, 8, 257)])
+@pytest.mark.parametrize("sign", [INVERSE, FORWARD])
+def test_rectangular_planes(F, nx, ny, nz, b, sign):
+    """Unequal x and y: both sides of every class of plane sizes, odd and even
+    rows, one- to three-stage lengths, planes too small for it; in place too."""
+    x = workloads.uniform_grid((nx, ny, nz), 1200 + nx + ny, batch=b)
+    plan = F.Plan(nx, ny, nz, b, "fp32", sign)
+    if nx != ny:
+        assert ("k_plane_rect" in plan.describe()) == (nx * ny >= 300 or b * nz <= 2048)
+    xt = torch.from_numpy(x).cuda()
+    y = plan.exec(xt)
+    assert torch.equal(xt.cpu(), torch.from_numpy(x))
+    z = xt.clone()
+    plan.exec(z, z)
+    assert torch.equal(y, z)
+    for j in {0, b // 2, b - 1}:
+        assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
