@@ -185,6 +185,15 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
     p->tw_ry = append(ny, -direction, kind);
     p->tw_rz = append(nz, -direction, kind);
     if (nx == ny && !q16 && !large) p->tw_zrev = append(nz, FFT3D_FORWARD, 3);
+    const bool split = large && nx == ny && ny == nz && split_batch_ok(nx, batch);
+    if (split) {
+        p->tw_n1 = append(nx / split_parts_of(nx), direction, 0);
+        p->tw_rt = (long)tab.size();
+        for (int m = 0; m < nx; ++m) {
+            const double a = 2.0 * M_PI * (double)m / (double)nx;
+            tab.push_back(make_float2((float)std::cos(a), (float)(direction * std::sin(a))));
+        }
+    }
     if (tab.empty()) tab.push_back(make_float2(0.f, 0.f));
     const size_t bytes = tab.size() * sizeof(float2);
     if (test_fail_alloc() || hipMalloc((void**)&p->d_tw, bytes) != hipSuccess) {
@@ -279,6 +288,10 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
             p->passes.push_back({Pass::kPlaneK, nx, B * nz, {}, p->tw_x});
         }
         if (nz > 1) p->passes.push_back({Pass::kStrK, nz, 0, zmap, p->tw_z});
+    } else if (split) {
+        const int cus = device_cus(dev);
+        p->passes.push_back({Pass::kSplitPlaneK, nx, B * nz, {}, p->tw_x, cus});
+        p->passes.push_back({Pass::kSplitZK, nx, B, {}, p->tw_z, cus});
     } else if (rect_init(nx, ny, B * nz, direction)) {
         // the plane in LDS, as one pass (nx != ny, or a larger nz)
         p->passes.push_back({Pass::kRectK, nx, B * nz, {}, p->tw_x});
@@ -413,6 +426,10 @@ static hipError_t run_pass(const fft3d_plan_s* p, const Pass& ps, const float2* 
     switch (ps.kind) {
     case Pass::kCubeK: return cube_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kCubeLinesK: return cube_lines_fn(ps.n, S)(src, dst, tw, ps.count, st);
+    case Pass::kSplitPlaneK:
+        return split_plane_fn(ps.n, S)(src, dst, tw, p->d_tw + p->tw_n1, ps.count, ps.grid, st);
+    case Pass::kSplitZK:   // in place on the output (as every pass but the first)
+        return split_z_fn(ps.n, S)(dst, tw, p->d_tw + p->tw_rt, ps.count, ps.grid, st);
     case Pass::kRectK:
         return launch_plane_rect(src, dst, p->d_tw + p->tw_x, p->d_tw + p->tw_y, p->nx, p->ny, ps.count, S, st);
     case Pass::kPlaneK: return plane_fn(ps.n, S)(src, dst, tw, ps.count, st);
@@ -1046,7 +1063,8 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
     for (size_t i = 0; i < p->passes.size(); ++i) {
         static const char* names[] = {"k_cube",      "k_plane",    "k_plane_pf",     "k_axis_row",
                                       "k_axis_str",  "k_fused",    "k_q16_plane",    "k_q16_slab",
-                                      "k_plane_pruned", "k_axis_str_pruned", "k_plane_real", "k_cube_lines", "k_plane_rect"};
+                                      "k_plane_pruned", "k_axis_str_pruned", "k_plane_real", "k_cube_lines", "k_plane_rect",
+                                      "k_split_plane", "k_split_z"};
         d += (i ? "," : "") + std::string(names[p->passes[i].kind]);
     }
     if (buf && len) {

@@ -28,12 +28,12 @@ int twiddles_into(float2* t, int cap, int n, int sign, int kind = 0);
 // every later pass works in place on the output buffer.
 struct Pass {
     enum Kind { kCubeK, kPlaneK, kPlanePfK, kRowK, kStrK, kFusedK, kQ16PlaneK, kQ16SlabK, kPlanePrunedK, kStrPrunedK, kRealK,
-                kCubeLinesK, kRectK } kind;
+                kCubeLinesK, kRectK, kSplitPlaneK, kSplitZK } kind;
     int n;        // transform length of this pass
     long count;   // grids / planes / rows (cube, plane, row kinds)
     AxisMap map;  // strided kind
     long tw;      // offset of this pass's twiddle table in d_tw
-    int grid;     // workgroups of a persistent launch
+    int grid;     // workgroups of a persistent launch (split kinds: compute units)
 };
 
 // Heterogeneous batch (fft3d_plan_many): groups of cubic grids, one
@@ -96,7 +96,9 @@ struct fft3d_plan_s {
     long sphere_pts;           // points per grid inside the cutoff sphere
     std::vector<fft3d::Pass> dense_passes;   // schedule without the cutoff
     bool real;                 // plan from fft3d_plan_real (r2c forward / c2r inverse)
-    long tw_rt;                // real plans: offset of the split/merge roots W_N^{direction*k}, k <= N/4
+    long tw_rt;                // real plans: offset of the split/merge roots W_N^{direction*k}, k <= N/4;
+                               // split form: of the roots W_N^{direction*k}, k < N
+    long tw_n1;                // split form: offset of the length N / parts table
     bool many;                 // plan from fft3d_plan_many
     fft3d::ManyPlan mp;
 };

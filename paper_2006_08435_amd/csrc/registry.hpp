@@ -135,6 +135,18 @@ hipError_t rect_inv(int cls, const RectArgs& a, unsigned grid, size_t lds, hipSt
 const void* rect_fwd_kernel(int cls);
 const void* rect_inv_kernel(int cls);
 
+// Two-pass form of cubic grids of 129 to 256 points a side (kernels_split.hpp;
+// nullptr / 0: a length without it).  tw_x: the length-n table, tw_y the table
+// of length n / split_parts_of(n), root[m] = exp(sign 2 pi i m / n), m < n.
+using SplitPlaneFn = hipError_t (*)(const float2* in, float2* out, const float2* tw_x, const float2* tw_y, long planes,
+                                    int cus, hipStream_t st);
+using SplitZFn = hipError_t (*)(float2* buf, const float2* tw_z, const float2* root, long grids, int cus,
+                                hipStream_t st);
+SplitPlaneFn split_plane_fn(int n, int sign);
+SplitZFn split_z_fn(int n, int sign);
+int split_parts_of(int n);
+bool split_batch_ok(int n, int batch);
+
 // Heterogeneous persistent kernel (kernels_many.hpp); threads is 512 or 1024.
 hipError_t launch_many(const ManyArgs& a, int sign, int threads, int grid, size_t lds_bytes, hipStream_t st);
 int many_blocks_per_cu(int threads, size_t lds_bytes);

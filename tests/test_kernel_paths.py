@@ -220,3 +220,35 @@ def test_rectangular_planes(F, nx, ny, nz, b, sign):
     assert torch.equal(y, z)
     for j in {0, b // 2, b - 1}:
         assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
+
+
+@pytest.mark.parametrize("n,b", [(135, 1), (144, 2), (150, 1), (160, 1), (162, 1), (180, 1), (192, 1), (200, 1), (216, 1),
+                                 (225, 1), (240, 2), (240, 3), (243, 1), (250, 1), (256, 1)])
+def test_two_passes_above_128(F, n, b):
+    """Every length of the two-pass form (whole and ragged x tiles, one and two
+    points a load) and its neighbours without one: out of place, in place, and
+    pass by pass."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.view_as_complex(torch.rand((b, n, n, n, 2), generator=gen, device="cuda") - 0.5)
+    lib = F._lib.lib()
+    s = torch.cuda.current_stream().cuda_stream
+    two = n not in (225, 243, 250) and (n != 240 or b > 2)
+    for sign in (INVERSE, FORWARD):
+        plan = F.Plan(n, n, n, b, "fp32", sign)
+        assert ("k_split_plane,k_split_z" in plan.describe()) == two
+        y = plan.exec(x)
+        z = x.clone()
+        plan.exec(z, z)
+        p = torch.empty_like(x)
+        for k in range(lib.fft3d_plan_passes(plan.handle)):
+            src = x if k == 0 else p
+            assert lib.fft3d_exec_pass(plan.handle, k, src.data_ptr(), p.data_ptr(), s) == 0
+        assert torch.equal(p, y)
+        q = x.clone()
+        for k in range(lib.fft3d_plan_passes(plan.handle)):
+            assert lib.fft3d_exec_pass(plan.handle, k, q.data_ptr(), q.data_ptr(), s) == 0
+        assert torch.equal(q, z)
+        for j in range(b):
+            want = oracle.fft3d(x[j].cpu().numpy().astype(np.complex128), sign)
+            assert rel(y[j].cpu().numpy(), want) <= TOL
+            assert rel(z[j].cpu().numpy(), want) <= TOL
