@@ -20,7 +20,7 @@ from __future__ import annotations
 import torch
 
 from . import _lib
-from . import FFT3D_FORWARD, FFT3D_INVERSE, fftn, get_plan, ifftn
+from . import FFT3D_FORWARD, FFT3D_INVERSE, _stream_handle, fftn, get_plan, ifftn
 
 
 class FFT3D(torch.autograd.Function):
@@ -65,7 +65,7 @@ class LocalPotentialEnergy(torch.autograd.Function):
         psi = torch.empty_like(cb)
         save_psi = bool(save_psi) and any(ctx.needs_input_grad)
         E = torch.empty((), dtype=torch.float64, device=cb.device)
-        sh = int(torch.cuda.current_stream().cuda_stream)
+        sh = _stream_handle()
         if save_psi:
             _lib.check(_lib.lib().fft3d_energy_vpsi_fwd(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
                                                         E.data_ptr(), sh), "fft3d_energy_vpsi_fwd")
@@ -83,7 +83,7 @@ class LocalPotentialEnergy(torch.autograd.Function):
         src, Vc = ctx.saved_tensors
         grad = torch.empty_like(src)
         g64 = gE.detach().to(torch.float64).reshape(()).contiguous()
-        sh = int(torch.cuda.current_stream().cuda_stream)
+        sh = _stream_handle()
         if ctx.have_psi:
             _lib.check(_lib.lib().fft3d_energy_vpsi_bwd(ctx.plan.handle, src.data_ptr(), g64.data_ptr(),
                                                         grad.data_ptr(), sh), "fft3d_energy_vpsi_bwd")
@@ -107,7 +107,7 @@ def energy(c, V):
     plan = get_plan(nx, ny, nz, b, "fp32", FFT3D_INVERSE)
     work = torch.empty_like(cb)
     E = torch.empty((), dtype=torch.float64, device=cb.device)
-    sh = int(torch.cuda.current_stream().cuda_stream)
+    sh = _stream_handle()
     _lib.check(_lib.lib().fft3d_energy(plan.handle, cb.data_ptr(), Vc.data_ptr(), work.data_ptr(), E.data_ptr(), sh),
                "fft3d_energy")
     return E
@@ -120,7 +120,7 @@ def energy_and_psi(c, V):
     plan = get_plan(nx, ny, nz, b, "fp32", FFT3D_INVERSE)
     psi = torch.empty_like(cb)
     E = torch.empty((), dtype=torch.float64, device=cb.device)
-    sh = int(torch.cuda.current_stream().cuda_stream)
+    sh = _stream_handle()
     _lib.check(_lib.lib().fft3d_energy_fwd(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
                                            E.data_ptr(), sh), "fft3d_energy_fwd")
     return E, (psi[0] if c.dim() == 3 else psi)
