@@ -732,6 +732,18 @@ k_plane_pruned(const float2* in, float2* out, const float2* __restrict__ tw, lon
     constexpr int T = PlaneGeom<N>::T, RS = PlaneGeom<N>::RS;
     __shared__ float2 lds[PlaneGeom<N>::WORDS];
     const int tid = threadIdx.x;
+    // per-lane twiddles from an LDS copy of the table, as in k_plane_pf (128
+    // orbitals at 96^3 with a cutoff: the density 253 -> 245 us).  Measured and
+    // not kept: two workgroups of 512 threads a compute unit without the
+    // prefetch, where two tiles fit (80 to 100 points): 253 -> 287, its
+    // registers spill.
+    constexpr int TWN = Plan1D<N>::tw_len;
+    constexpr bool TWL = N % 64 != 0 && TWN > 0;
+    __shared__ float2 tw_lds[TWL ? TWN : 1];
+    if constexpr (TWL) {
+        for (int i = tid; i < TWN; i += T) tw_lds[i] = tw[i];   // visible after the first barrier below
+        tw = tw_lds;
+    }
     typename std::conditional<PACKED, PackedRegs<N, T>, TileRegs<N, N, T, stream_plane(N)>>::type regs;
     auto plane_base = [&](long i) {
         if constexpr (OUT) return i * N * N;
