@@ -1549,8 +1549,9 @@ struct OrbitalRanges {
 // |psi_b(r)|^2, psi_b the inverse z-transform of orbital b of `buf` (already
 // transformed along x and y; orbitals `vol` apart).  Each workgroup owns L
 // adjacent z-lines of the grid (map: the lines of ONE grid) and loops over
-// the orbitals: stage 0 from HBM into LDS, the other stages in LDS, then each
-// thread adds occ[b] |psi|^2 at its fixed points in registers (FP32 FMA, in
+// the orbitals: stage 0 from HBM into LDS, the other stages in LDS, the last
+// one's values added as occ[b] |psi|^2 straight from its butterflies to sums
+// that stay in registers (FP32 FMA, in
 // fixed orbital order, last first: deterministic).  psi is never stored.  MODE 1
 // (cutoff R2): loads only of the planes with Gz^2 < R2 (the others were not
 // written by the pruned plane pass).
@@ -1572,7 +1573,6 @@ k_axis_density(float2* buf, const float2* __restrict__ tw, AxisMap m, long vol,
     using P = Plan1D<N>;
     constexpr int T = G::T;
     static_assert(T % L == 0, "each thread keeps one line");
-    constexpr int PER = (N * L + T - 1) / T;   // points per thread
     // stage 0 (radix R0, no twiddles) is split into its loads, issued one
     // orbital ahead into registers, and its butterflies
     constexpr int R0 = P::radix(0), M0 = N / R0, NB0 = L * M0, IT0 = (NB0 + T - 1) / T;
@@ -1614,48 +1614,69 @@ k_axis_density(float2* buf, const float2* __restrict__ tw, AxisMap m, long vol,
             }
         }
     };
-    float acc[PER];
+    // the last stage's butterflies are this thread's points: their values are
+    // squared and summed as they leave the butterfly
+    constexpr int ST = P::stages - 1, R = P::radix(ST), M = N / R, NB = L * M, IT = (NB + T - 1) / T;
+    float acc[IT][R];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) acc[k] = 0.f;
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int q = 0; q < R; ++q) acc[it][q] = 0.f;
     const LdsAcc<1, G::LP> a{lds};
     // orbitals from the last to the first: the plane pass before this one
     // wrote the last orbitals last, so they are the ones still in the caches
     load0(b1 - 1);
     for (int b = b1 - 1; b >= b0; --b) {
+        const float f = occ[b];
 #pragma unroll
         for (int it = 0; it < IT0; ++it) {
             const int bb = tid + it * T, j = bb / L;
             if ((NB0 % T == 0 || bb < NB0) && myline < valid) {
                 dft<R0, 1>(pre[it]);
 #pragma unroll
-                for (int q = 0; q < R0; ++q) lds[(j * R0 + q) * G::LP + myline] = pre[it][q];
+                for (int q = 0; q < R0; ++q) {
+                    const float2 p = pre[it][q];
+                    if constexpr (ST > 0) lds[(j * R0 + q) * G::LP + myline] = p;
+                    else acc[it][q] = fmaf(f, fmaf(p.x, p.x, p.y * p.y), acc[it][q]);
+                }
             }
         }
-        __syncthreads();
+        if constexpr (ST > 0) __syncthreads();
         if (b > b0) load0(b - 1);
-        if constexpr (P::stages > 1) {
-            run_tail<N, 1, L, T, 1, false>(a, a, tw, tid, valid);
-            __syncthreads();
-        }
-        const float f = occ[b];
+        if constexpr (ST > 1) { fft_stage<N, 1, 1, L, T, true, true>(a, a, tw, tid, valid); __syncthreads(); }
+        if constexpr (ST > 2) { fft_stage<N, 2, 1, L, T, true, true>(a, a, tw, tid, valid); __syncthreads(); }
+        if constexpr (ST > 0) {
+            const float2* tws = tw + P::tw_off(ST);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * T;
-            if ((N * L) % T == 0 || i < N * L) {
-                const float2 p = lds[(i / L) * G::LP + myline];
-                acc[k] = fmaf(f, fmaf(p.x, p.x, p.y * p.y), acc[k]);
+            for (int it = 0; it < IT; ++it) {
+                const int bb = tid + it * T, j = bb / L;
+                if ((NB % T == 0 || bb < NB) && myline < valid) {
+                    float2 v[R];
+#pragma unroll
+                    for (int q = 0; q < R; ++q) v[q] = lds[(j + q * M) * G::LP + myline];
+                    const float2* w = tws + j * (R - 1);
+#pragma unroll
+                    for (int q = 1; q < R; ++q) v[q] = cmul(v[q], w[q - 1]);
+                    dft<R, 1>(v);
+#pragma unroll
+                    for (int q = 0; q < R; ++q)
+                        acc[it][q] = fmaf(f, fmaf(v[q].x, v[q].x, v[q].y * v[q].y), acc[it][q]);
+                }
             }
+            __syncthreads();   // the next orbital's stage 0 overwrites the tile
         }
-        __syncthreads();   // the next orbital's stage 0 overwrites the tile
     }
     if (myline < valid) {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * T;
-            if ((N * L) % T == 0 || i < N * L) {
-                const long e = (long)(i / L) * m.es;
-                if (ranges.count == 1) rho[gbase + e] = acc[k];
-                else reinterpret_cast<float*>(buf + (long)b0 * vol + l0 + e)[myline] = acc[k];
+        for (int it = 0; it < IT; ++it) {
+            const int bb = tid + it * T, j = bb / L;
+            if (NB % T == 0 || bb < NB) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    const long e = (long)(j + q * M) * m.es;
+                    if (ranges.count == 1) rho[gbase + e] = acc[it][q];
+                    else reinterpret_cast<float*>(buf + (long)b0 * vol + l0 + e)[myline] = acc[it][q];
+                }
             }
         }
     }
