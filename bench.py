@@ -48,7 +48,8 @@ KERNEL_UNITS = {
     "k_axis_density": ("k_axis.hip",), "k_axis_energy": ("k_axis.hip",), "k_axis_hloc": ("k_axis.hip",),
     "k_sum_partials": ("k_axis.hip",), "k_sphere_": ("k_axis.hip",), "k_fused_xcd": ("k_fused.hip",),
     "k_many": ("k_many.hip",), "k_plane_r2c": ("k_real.hip",), "k_plane_c2r": ("k_real.hip",),
-    "k_stream_copy": ("k_copy.hip",), "k_q16_": ("k_q16.hip",),
+    "k_stream_copy": ("k_copy.hip",), "k_cube": ("k_cube.hip",), "k_density_sum": ("k_axis.hip",),
+    "k_plane_rect": ("k_rect.hip", "k_rect_fwd.hip", "k_rect_inv.hip"), "k_split_": ("k_split.hip",), "k_q16_": ("k_q16.hip",),
 }
 HOST_UNITS = ("fft3d_api.cpp",)
 # the batched form's planner (work lists, schedules, tuner) launches these too
@@ -788,9 +789,9 @@ def bench_energy(args):
                            "E_only_rel": abs(E_only_value - E_all) / abs(E_all)},
         # unit: the energy forward (one read of c, one write of psi; V, 3.4 MB,
         # and the partial sums are not counted)
-        "roofline": transform_roofline(alg, fwd_ms, "energy_fwd: k_plane_pf<96, 1, false, true> + "
+        "roofline": transform_roofline(alg, fwd_ms, "energy_fwd: k_plane_pf<96, 1, 0, true> + "
                                        "k_axis_str<96, 1, 64, true, 0> + k_sum_partials",
-                                       traffic_sum("energy96", ["k_plane_pf<96, 1, false, true",
+                                       traffic_sum("energy96", ["k_plane_pf<96, 1, 0, true",
                                                                 "k_axis_str<96, 1, 64, true, 0"]),
                                        launches=3),
         "cpu_baseline": None if args.no_cpu_baseline else _cpu_oracle(c, n, 1, args.cpu_seconds, "96^3 orbitals"),

@@ -428,8 +428,8 @@ static hipError_t run_pass(const fft3d_plan_s* p, const Pass& ps, const float2* 
     case Pass::kCubeLinesK: return cube_lines_fn(ps.n, S)(src, dst, tw, ps.count, st);
     case Pass::kSplitPlaneK:
         return split_plane_fn(ps.n, S)(src, dst, tw, p->d_tw + p->tw_n1, ps.count, ps.grid, st);
-    case Pass::kSplitZK:   // in place on the output (as every pass but the first)
-        return split_z_fn(ps.n, S)(dst, tw, p->d_tw + p->tw_rt, ps.count, ps.grid, st);
+    case Pass::kSplitZK:
+        return split_z_fn(ps.n, S)(src, dst, tw, p->d_tw + p->tw_rt, ps.count, ps.grid, st);
     case Pass::kRectK:
         return launch_plane_rect(src, dst, p->d_tw + p->tw_x, p->d_tw + p->tw_y, p->nx, p->ny, ps.count, S, st);
     case Pass::kPlaneK: return plane_fn(ps.n, S)(src, dst, tw, ps.count, st);

@@ -141,7 +141,8 @@ int apply_schedule(fft3d_plan_s* p, int threads, int chunk, const bool* plain = 
 // bytes.  The cheapest of three splits is taken: every group plain, the groups
 // that gain by it in one persistent launch, every group there.  Measured (us;
 // persistent launch of everything / plain launches / this rule):
-//   64^3 x 256 + 48 + 72 + 96 + 100 + 120        420 / 399 / 385 (the five single grids together)
+//   64^3 x 256 + 48 + 72 + 96 + 100 + 120        420 / 399 / 385 (the five single grids together;
+//                                                421 / 432 / 417 on buffers new to the caches)
 //   100 x 5 + 128 + 72 + 80 x 11 + 96 x 3 + 120 x 5   240 / 187 / plain
 //   36 x 240 + 50 x 145 + 100 x 7              353 / 207 / plain
 //   24 x 25 + 50                                28 /  19 / plain

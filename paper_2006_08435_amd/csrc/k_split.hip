@@ -28,13 +28,13 @@ static hipError_t launch_split_plane(const float2* in, float2* out, const float2
 }
 
 template <int N, int S>
-static hipError_t launch_split_z(float2* buf, const float2* tw_z, const float2* root, long grids, int cus,
-                                 hipStream_t st)
+static hipError_t launch_split_z(const float2* in, float2* out, const float2* tw_z, const float2* root, long grids,
+                                 int cus, hipStream_t st)
 {
     using G = SplitGeom<N>;
     const long tiles = grids * G::N1 * G::XT;
-    hipLaunchKernelGGL((k_split_z<N, S>), dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(G::T), 0, st, buf, tw_z,
-                       root, tiles);
+    hipLaunchKernelGGL((k_split_z<N, S>), dim3((unsigned)(tiles < cus ? tiles : cus)), dim3(G::T), 0, st, in, out,
+                       tw_z, root, tiles);
     return hipGetLastError();
 }
 

@@ -187,10 +187,10 @@ k_split_y(float2* buf, const float2* __restrict__ tw_y)
 }
 
 // Pass two: tile t = (grid, k1, x tile), persistent with the next tile's points
-// in flight, in place on buf.  root[m] = W_N^m.
+// in flight; in == out allowed.  root[m] = W_N^m.
 template <int N, int S>
 __global__ void __launch_bounds__(SplitGeom<N>::T)
-k_split_z(float2* buf, const float2* __restrict__ tw_z, const float2* __restrict__ root, long tiles)
+k_split_z(const float2* in, float2* out, const float2* __restrict__ tw_z, const float2* __restrict__ root, long tiles)
 {
     using G = SplitGeom<N>;
     constexpr int R = G::R, N1 = G::N1, T = G::T, L = G::L, LINES = G::LINES, LP = G::LP, XT = G::XT, VEC = G::VEC;
@@ -218,7 +218,7 @@ k_split_z(float2* buf, const float2* __restrict__ tw_z, const float2* __restrict
     typedef float fv __attribute__((ext_vector_type(2 * VEC)));
     fv r[IT][R];
     auto load = [&](const Where& w) {
-        const float2* src = buf + w.base + w.k1 * N + w.x0;
+        const float2* src = in + w.base + w.k1 * N + w.x0;
 #pragma unroll
         for (int k = 0; k < IT; ++k) {
             const int i = tid + k * T, z = i / LV, x = (i - z * LV) * VEC;
@@ -269,7 +269,7 @@ k_split_z(float2* buf, const float2* __restrict__ tw_z, const float2* __restrict
             }
         };
         const LdsAcc<1, LP> a{lds};
-        const Out o{buf + here.base + here.k1 * N + here.x0, N - here.x0};
+        const Out o{out + here.base + here.k1 * N + here.x0, N - here.x0};
         run_tail<N, S, LINES, T, 0, false>(a, o, tw_z, tid);
         __syncthreads();
     }

@@ -140,8 +140,8 @@ const void* rect_inv_kernel(int cls);
 // of length n / split_parts_of(n), root[m] = exp(sign 2 pi i m / n), m < n.
 using SplitPlaneFn = hipError_t (*)(const float2* in, float2* out, const float2* tw_x, const float2* tw_y, long planes,
                                     int cus, hipStream_t st);
-using SplitZFn = hipError_t (*)(float2* buf, const float2* tw_z, const float2* root, long grids, int cus,
-                                hipStream_t st);
+using SplitZFn = hipError_t (*)(const float2* in, float2* out, const float2* tw_z, const float2* root, long grids,
+                                int cus, hipStream_t st);
 SplitPlaneFn split_plane_fn(int n, int sign);
 SplitZFn split_z_fn(int n, int sign);
 int split_parts_of(int n);

@@ -244,6 +244,14 @@ def test_two_passes_above_128(F, n, b):
             src = x if k == 0 else p
             assert lib.fft3d_exec_pass(plan.handle, k, src.data_ptr(), p.data_ptr(), s) == 0
         assert torch.equal(p, y)
+        # the last pass from one buffer into another, its input left alone
+        assert lib.fft3d_exec_pass(plan.handle, 0, x.data_ptr(), p.data_ptr(), s) == 0
+        for k in range(1, lib.fft3d_plan_passes(plan.handle) - 1):
+            assert lib.fft3d_exec_pass(plan.handle, k, p.data_ptr(), p.data_ptr(), s) == 0
+        mid, last = p.clone(), torch.empty_like(p)
+        k = lib.fft3d_plan_passes(plan.handle) - 1
+        assert lib.fft3d_exec_pass(plan.handle, k, p.data_ptr(), last.data_ptr(), s) == 0
+        assert torch.equal(last, y) and torch.equal(p, mid)
         q = x.clone()
         for k in range(lib.fft3d_plan_passes(plan.handle)):
             assert lib.fft3d_exec_pass(plan.handle, k, q.data_ptr(), q.data_ptr(), s) == 0
@@ -252,3 +260,50 @@ def test_two_passes_above_128(F, n, b):
             want = oracle.fft3d(x[j].cpu().numpy().astype(np.complex128), sign)
             assert rel(y[j].cpu().numpy(), want) <= TOL
             assert rel(z[j].cpu().numpy(), want) <= TOL
+
+
+@pytest.mark.parametrize("form", ["lines", "rows", "split", "density", "energy", "spheres"])
+def test_captured_and_replayed(F, form):
+    """The forms above from a HIP graph, replayed with new inputs and eager work
+    in between, against the eager call bit for bit."""
+    shape, b = {"lines": ((20, 20, 20), 3), "rows": ((100, 72, 5), 2), "split": ((135, 135, 135), 1),
+                "density": ((24, 24, 6), 20), "energy": ((30, 30, 6), 3), "spheres": ((18, 18, 6), 2)}[form]
+    n = shape[0]
+    plan = F.Plan(*shape, b, "fp32", INVERSE)
+    if form == "spheres":
+        plan.set_cutoff((n / 4) ** 2)
+    xs = [torch.from_numpy(workloads.uniform_grid(shape, 1300 + k, batch=b)).cuda() for k in range(3)]
+    V = torch.from_numpy(workloads.uniform_grid(shape, 1299).real.copy()).cuda()
+    occ = torch.linspace(0.5, 2.0, b, device="cuda")
+    x = torch.empty_like(xs[0])
+    out, work, E = torch.empty_like(x), torch.empty_like(x), torch.zeros((), dtype=torch.float64, device="cuda")
+    rho = torch.empty(V.shape, dtype=torch.float32, device="cuda")
+    lib = F._lib.lib()
+
+    def call():
+        if form == "density":
+            return plan.density(x, occ, rho, work)
+        if form == "energy":
+            s = torch.cuda.current_stream().cuda_stream
+            assert lib.fft3d_energy_vpsi_fwd(plan.handle, x.data_ptr(), V.data_ptr(), work.data_ptr(), E.data_ptr(),
+                                             s) == 0
+            assert lib.fft3d_energy_vpsi_bwd(plan.handle, work.data_ptr(), E.data_ptr(), out.data_ptr(), s) == 0
+            return out
+        if form == "spheres":
+            return plan.unpack(plan.pack(x, packed), out)
+        return plan.exec(x, out)
+
+    packed = torch.empty((b, plan.sphere_points), dtype=torch.complex64, device="cuda") if form == "spheres" else None
+    want = []
+    for v in xs:
+        x.copy_(v)
+        want.append(call().clone())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        got = call()
+    for k in (0, 1, 2, 1):
+        x.copy_(xs[k])
+        got.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want[k]), k
