@@ -1258,6 +1258,20 @@ struct GlobZPacked {
 // step, with the plane pass's stores left in the caches (default policy).
 __device__ __forceinline__ long rev_tile() { return (long)(gridDim.x - 1 - blockIdx.x); }
 
+// rev_tile with the tiles of one grid dealt to the XCDs in runs: eight runs of
+// c tiles make about a grid, and the workgroups b, b + 8, b + 16, .. (one XCD)
+// take the tiles of one run.  So neighbouring tiles, which share a cache line
+// at each of their ends where rows are not whole cache lines, and the same part
+// of V for grid after grid meet in one L2.  `lines` are a grid's.  The last part
+// of the launch, which fills no group of 8 c, stays in launch order.
+__device__ __forceinline__ long rev_tile_runs(unsigned lines, int L)
+{
+    const unsigned b = gridDim.x - 1 - blockIdx.x;
+    if (lines < 4 * L) return b;
+    const unsigned c = (lines + 4 * L) / (8 * L), group = 8 * c, g0 = b / group * group, r = b - g0;
+    return g0 + group > gridDim.x ? b : g0 + r % 8 * c + r / 8;
+}
+
 // ENERGY: the pass is the last one of an inverse transform psi = IFFT(c);
 // while storing psi it accumulates sum V |psi|^2 and writes one FP64 partial
 // per tile to partials[tile] (V indexed by position in the grid).
@@ -1440,7 +1454,16 @@ k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __rest
     __shared__ float2 lds[ST > 0 ? G::WORDS : 1];
     __shared__ double red[T / 64];
     const int tid = threadIdx.x;
-    const long tile = rev_tile();
+    // Runs of tiles for an XCD, but where 8 L divides a grid's lines: there the
+    // launch order already gives an XCD the same part of V for every grid and
+    // whole cache lines.  The pruned form takes them for rows that are not whole
+    // cache lines only.  Measured, launch order -> runs, us: E and gradient of
+    // 64 x 90^3 446 -> 418, 64 x 81^3 348 -> 319, 200 x 50^3 219 -> 213,
+    // 64 x 100^3 575 -> 562, 128 x 72^3 420 -> 409; packed H psi of 64 x 90^3
+    // 359 -> 354, of 64 x 80^3 (whole cache lines) 249 -> 251.
+    const unsigned grid_lines = (unsigned)m.nx * (unsigned)m.odiv;
+    const bool runs = MODE == 1 ? grid_lines % 16 != 0 : grid_lines % (8 * L) != 0;
+    const long tile = runs ? rev_tile_runs(grid_lines, L) : rev_tile();
     const long l0 = tile * L;
     const int myline = tid % L;
     const long li = l0 + myline;

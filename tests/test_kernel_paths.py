@@ -70,6 +70,34 @@ def test_operator_lengths(F, nz, cut):
     assert abs(E.item() - E_ref) <= 1e-6 * abs(E_ref)
 
 
+@pytest.mark.parametrize("cut", [False, True])
+@pytest.mark.parametrize("n,nz,b", [(15, 3, 9), (16, 3, 9), (18, 3, 1), (18, 3, 2), (18, 3, 11), (30, 4, 9), (50, 2, 1),
+                                    (90, 2, 1), (90, 2, 2)])
+def test_operator_tile_order(F, n, nz, b, cut):
+    """Tiles taken in runs of an XCD: grids of fewer lines than eight runs
+    have, one group short of full, exactly one, and several with a rest."""
+    r2 = (0.3 * n) ** 2
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + workloads.signed_freq(nz)[:, None, None] ** 2) < r2
+    c = workloads.uniform_grid((n, n, nz), 500 + n, batch=b)
+    if cut:
+        c = (c * inside).astype(np.complex64)
+    V = (workloads.uniform_grid((n, n, nz), 600 + n).real + 1.5).astype(np.float32)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    if cut:
+        plan.set_cutoff(r2)
+    E = torch.zeros((), dtype=torch.float64, device="cuda")
+    out = plan.apply_potential(torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda(), E=E).cpu().numpy()
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    want = np.fft.fftn(V.astype(np.float64) * psi, axes=(1, 2, 3))
+    if cut:
+        out, want = out[:, inside], want[:, inside]
+    for k in range(b):
+        assert rel(out[k], want[k]) <= TOL, k
+    E_ref = float((V.astype(np.float64) * np.abs(psi) ** 2).sum())
+    assert abs(E.item() - E_ref) <= 1e-6 * abs(E_ref)
+
+
 @pytest.mark.parametrize("n,nz,b,r2", [(1, 1, 3, 1.0), (2, 3, 2, 0.5), (3, 2, 5, 1e9), (8, 8, 300, 4.0), (15, 4, 2, 14.0),
                                        (16, 5, 3, 1e9), (90, 3, 2, 0.1), (90, 2, 2, 506.25), (125, 2, 1, 3844.0)])
 def test_sphere_copies(F, n, nz, b, r2):
