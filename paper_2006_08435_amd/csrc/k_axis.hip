@@ -42,23 +42,27 @@ static hipError_t launch_axis_str(const float2* in, float2* out, const float2* t
     const long blocks = axis_str_blocks(m.lines);
     if (energy == 2) {
         hipLaunchKernelGGL((k_axis_energy<N, S, kAxisLines>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, tw, m, V, partials, vol);
+                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, tw, in_runs(m, blocks, kAxisLines, true), V,
+                           partials, vol);
         return hipGetLastError();
     }
     if (energy)
         hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, true>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw, m, V, partials, vol, 0.0);
+                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw,
+                           in_runs(m, blocks, kAxisLines, true), V, partials, vol, 0.0);
     else
         hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw, m, V, partials, vol, 0.0);
+                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw,
+                           in_runs(m, blocks, kAxisLines, false), V, partials, vol, 0.0);
     return hipGetLastError();
 }
 
 template <int N, int S>
-static hipError_t launch_axis_str_pruned(const float2* in, float2* out, const float2* tw, const AxisMap& m, double R2,
-                                         const SphereRow* rows, long npts, hipStream_t st)
+static hipError_t launch_axis_str_pruned(const float2* in, float2* out, const float2* tw, const AxisMap& map,
+                                         double R2, const SphereRow* rows, long npts, hipStream_t st)
 {
-    const long blocks = axis_str_blocks(m.lines);
+    const long blocks = axis_str_blocks(map.lines);
+    const AxisMap m = in_runs(map, blocks, kAxisLines, false);
     // inverse plans prune the loads (sphere-limited input), forward plans
     // lines and stores (optionally scattering into a packed sphere)
     if constexpr (S < 0) {
@@ -89,11 +93,13 @@ AxisStrPrunedFn axis_str_pruned_fn(int n, int sign)
 }
 
 template <int N>
-static hipError_t launch_hloc(float2* buf, const float2* tw_inv, const float2* tw_fwd, const AxisMap& m,
+static hipError_t launch_hloc(float2* buf, const float2* tw_inv, const float2* tw_fwd, const AxisMap& map,
                               const float* V, const double* scale, float mult, double* partials, long vol, double R2,
                               int mode, hipStream_t st)
 {
-    const long blocks = axis_str_blocks(m.lines);
+    const long blocks = axis_str_blocks(map.lines);
+    // the pruned form gains from whole cache lines only (64 x 80^3 249 us, in runs 251)
+    const AxisMap m = in_runs(map, blocks, kAxisLines, mode == 0);
     if (mode)
         hipLaunchKernelGGL((k_axis_hloc<N, kAxisLines, 1>), dim3((unsigned)blocks), dim3(AxisGeom<N, kAxisLines>::T),
                            0, st, buf, tw_inv, tw_fwd, m, V, scale, mult, partials, vol, R2);

@@ -29,7 +29,7 @@ static hipError_t launch_str_large(const float2* in, float2* out, const float2* 
     constexpr int L = large_lines<N>();
     const long blocks = (m.lines + L - 1) / L;
     hipLaunchKernelGGL((k_axis_str<N, S, L, false>), dim3((unsigned)blocks), dim3(AxisGeom<N, L>::T), 0, st, in, out,
-                       tw, m, nullptr, nullptr, 0L, 0.0, nullptr, 0L);
+                       tw, in_runs(m, blocks, L, false), nullptr, nullptr, 0L, 0.0, nullptr, 0L);
     return hipGetLastError();
 }
 

@@ -1148,7 +1148,28 @@ struct AxisMap {
     int nx;
     int odiv;
     long shi, slo, es;
+    int run = 0;     // tiles of an XCD's run (z_tile), 0: launch order
 };
+
+// The map of a strided pass of `tiles` tiles of L lines with its order of
+// tiles.  Where rows are not whole cache lines (with_V: or an XCD would meet
+// another part of V in every grid, as 8 L does not divide a grid's lines), the
+// tiles of one grid are dealt to the XCDs in runs of an eighth of a grid: then
+// neighbouring tiles, which share a cache line at each of their ends, and the
+// same part of V for grid after grid meet in one L2.  A launch that the device
+// holds at once keeps launch order (one 90^3 25.4 us, in runs 26.0).  Measured,
+// launch order -> runs, us, inverse and forward: 60 x 81^3 394 -> 367,
+// 100 x 75^3 492 -> 465, 400 x 50^3 569 -> 548, 32 x 90^3 282 -> 273,
+// 4 x 243^3 1224 -> 1133, 375^3 1150 -> 1087, 64 x 90^3 r2c and c2r 303 -> 293;
+// with V, E and gradient: 64 x 90^3 446 -> 418, 64 x 81^3 348 -> 319, 64 x 100^3
+// 575 -> 562, 128 x 72^3 420 -> 409, without psi 64 x 90^3 680 -> 644.
+inline AxisMap in_runs(AxisMap m, long tiles, int L, bool with_V)
+{
+    const long lines = (long)m.nx * m.odiv;   // of a grid
+    const bool gains = m.es % 16 != 0 || (with_V && lines % (8 * L) != 0);
+    m.run = gains && tiles >= 512 && lines >= 4 * L ? (int)((lines + 4 * L) / (8 * L)) : 0;
+    return m;
+}
 
 template <int N, int L>
 struct AxisGeom {
@@ -1258,18 +1279,16 @@ struct GlobZPacked {
 // step, with the plane pass's stores left in the caches (default policy).
 __device__ __forceinline__ long rev_tile() { return (long)(gridDim.x - 1 - blockIdx.x); }
 
-// rev_tile with the tiles of one grid dealt to the XCDs in runs: eight runs of
-// c tiles make about a grid, and the workgroups b, b + 8, b + 16, .. (one XCD)
-// take the tiles of one run.  So neighbouring tiles, which share a cache line
-// at each of their ends where rows are not whole cache lines, and the same part
-// of V for grid after grid meet in one L2.  `lines` are a grid's.  The last part
-// of the launch, which fills no group of 8 c, stays in launch order.
-__device__ __forceinline__ long rev_tile_runs(unsigned lines, int L)
+// Tile of this workgroup under the map's order (in_runs): rev_tile, or within
+// each group of 8 run tiles, workgroups b, b + 8, b + 16, .. (one XCD) take run
+// neighbouring tiles.  The last part of the launch, which fills no group, stays
+// in launch order.
+__device__ __forceinline__ long z_tile(const AxisMap& m)
 {
     const unsigned b = gridDim.x - 1 - blockIdx.x;
-    if (lines < 4 * L) return b;
-    const unsigned c = (lines + 4 * L) / (8 * L), group = 8 * c, g0 = b / group * group, r = b - g0;
-    return g0 + group > gridDim.x ? b : g0 + r % 8 * c + r / 8;
+    if (__builtin_expect(m.run == 0, 1)) return b;
+    const unsigned run = (unsigned)m.run, group = 8 * run, g0 = b / group * group, r = b - g0;
+    return g0 + group > gridDim.x ? b : g0 + r % 8 * run + r / 8;
 }
 
 // ENERGY: the pass is the last one of an inverse transform psi = IFFT(c);
@@ -1305,7 +1324,7 @@ k_axis_str(const float2* in, float2* out, const float2* __restrict__ tw, AxisMap
         for (int i = tid; i < P::tw_len; i += T) tw_lds[i] = tw[i];
         tw = tw_lds;
     }
-    const long tile = rev_tile();
+    const long tile = z_tile(m);
     const long l0 = tile * L;
     const int myline = tid % L;
     const long li = l0 + myline;
@@ -1393,7 +1412,7 @@ k_axis_energy(const float2* in, const float2* __restrict__ tw, AxisMap m, const 
     __shared__ float2 lds[P::stages > 1 ? G::WORDS : 1];
     __shared__ double red[T / 64];
     const int tid = threadIdx.x;
-    const long tile = rev_tile();
+    const long tile = z_tile(m);
     const long l0 = tile * L;
     const long li = l0 + tid % L;
     const int valid = (int)((m.lines - l0) < L ? (m.lines - l0) : L);
@@ -1454,16 +1473,7 @@ k_axis_hloc(float2* buf, const float2* __restrict__ tw_inv, const float2* __rest
     __shared__ float2 lds[ST > 0 ? G::WORDS : 1];
     __shared__ double red[T / 64];
     const int tid = threadIdx.x;
-    // Runs of tiles for an XCD, but where 8 L divides a grid's lines: there the
-    // launch order already gives an XCD the same part of V for every grid and
-    // whole cache lines.  The pruned form takes them for rows that are not whole
-    // cache lines only.  Measured, launch order -> runs, us: E and gradient of
-    // 64 x 90^3 446 -> 418, 64 x 81^3 348 -> 319, 200 x 50^3 219 -> 213,
-    // 64 x 100^3 575 -> 562, 128 x 72^3 420 -> 409; packed H psi of 64 x 90^3
-    // 359 -> 354, of 64 x 80^3 (whole cache lines) 249 -> 251.
-    const unsigned grid_lines = (unsigned)m.nx * (unsigned)m.odiv;
-    const bool runs = MODE == 1 ? grid_lines % 16 != 0 : grid_lines % (8 * L) != 0;
-    const long tile = runs ? rev_tile_runs(grid_lines, L) : rev_tile();
+    const long tile = z_tile(m);
     const long l0 = tile * L;
     const int myline = tid % L;
     const long li = l0 + myline;

@@ -98,6 +98,31 @@ def test_operator_tile_order(F, n, nz, b, cut):
     assert abs(E.item() - E_ref) <= 1e-6 * abs(E_ref)
 
 
+@pytest.mark.parametrize("n,nz,b", [(15, 2, 146), (18, 2, 100), (18, 2, 101), (18, 2, 103), (25, 3, 60), (50, 2, 14), (90, 2, 5)])
+def test_tile_order(F, n, nz, b):
+    """The z passes' tiles in runs of an XCD, launches of just under and over
+    the 512 tiles from which they are taken, whole groups and rests: the plain
+    and the energy form."""
+    c = workloads.uniform_grid((n, n, nz), 700 + n, batch=b)
+    V = (workloads.uniform_grid((n, n, nz), 800 + n).real + 1.5).astype(np.float32)
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    x, v = torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda()
+    want = float((V.astype(np.float64) * np.abs(psi) ** 2).sum())
+    out = F.ifftn(x).cpu().numpy()
+    E, psi_e = F.energy_and_psi(x, v)
+    psi_e = psi_e.cpu().numpy()
+    for k in range(b):
+        assert rel(out[k], psi[k]) <= TOL, k
+        assert rel(psi_e[k], psi[k]) <= TOL, k
+    assert abs(E.item() - want) <= 1e-6 * want
+    assert abs(F.energy(x, v).item() - want) <= 1e-6 * want
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    op = plan.apply_potential(x, v, E=torch.zeros((), dtype=torch.float64, device="cuda")).cpu().numpy()
+    want = np.fft.fftn(V.astype(np.float64) * psi, axes=(1, 2, 3))
+    for k in range(b):
+        assert rel(op[k], want[k]) <= TOL, k
+
+
 @pytest.mark.parametrize("n,nz,b,r2", [(1, 1, 3, 1.0), (2, 3, 2, 0.5), (3, 2, 5, 1e9), (8, 8, 300, 4.0), (15, 4, 2, 14.0),
                                        (16, 5, 3, 1e9), (90, 3, 2, 0.1), (90, 2, 2, 506.25), (125, 2, 1, 3844.0)])
 def test_sphere_copies(F, n, nz, b, r2):
