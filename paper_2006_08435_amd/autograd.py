@@ -9,11 +9,12 @@
   fft3d_energy_vpsi_fwd: an inverse transform whose last pass sums E,
   multiplies psi by V and runs the gradient's z transform on it; that product
   is what the backward keeps (the memory of one psi), and fft3d_energy_vpsi_bwd
-  finishes it in one pass.  With save_psi=False, or when no gradient is
-  asked for, the forward is fft3d_energy (E only, nothing of psi written) and
-  the backward recomputes psi inside the fused operator.  Gradients follow
-  PyTorch's convention for real functions of complex tensors:
-  dE/dRe(c) + i dE/dIm(c).
+  finishes it in one pass.  With save_psi=False the forward is fft3d_energy
+  (E only, nothing of psi written) and the backward recomputes psi inside the
+  fused operator.  Where no gradient can be asked for c (grad mode is off, or
+  c does not require one) the forward is fft3d_energy too, whatever save_psi
+  says.  Gradients follow PyTorch's convention for real functions of complex
+  tensors: dE/dRe(c) + i dE/dIm(c); V has none.
 """
 from __future__ import annotations
 
@@ -63,7 +64,9 @@ class LocalPotentialEnergy(torch.autograd.Function):
         # V psi transformed along z (the gradient's first half), or the
         # intermediate of the E-only pass
         psi = torch.empty_like(cb)
-        save_psi = bool(save_psi) and any(ctx.needs_input_grad)
+        # needs_input_grad tells only what the inputs require; grad mode is read
+        # by local_potential_energy, as it is always off in here
+        save_psi = bool(save_psi) and ctx.needs_input_grad[0]
         E = torch.empty((), dtype=torch.float64, device=cb.device)
         sh = _stream_handle()
         if save_psi:
@@ -72,7 +75,8 @@ class LocalPotentialEnergy(torch.autograd.Function):
         else:   # psi is recomputed by the backward: E alone, psi never written
             _lib.check(_lib.lib().fft3d_energy(plan.handle, cb.data_ptr(), Vc.data_ptr(), psi.data_ptr(),
                                                E.data_ptr(), sh), "fft3d_energy")
-        ctx.save_for_backward(psi if save_psi else cb, Vc)
+        if ctx.needs_input_grad[0]:
+            ctx.save_for_backward(psi if save_psi else cb, Vc)
         ctx.have_psi = save_psi
         ctx.squeeze = c.dim() == 3
         ctx.plan = plan
@@ -80,6 +84,8 @@ class LocalPotentialEnergy(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gE):
+        if not ctx.needs_input_grad[0]:   # V alone requires one
+            return None, None, None
         src, Vc = ctx.saved_tensors
         grad = torch.empty_like(src)
         g64 = gE.detach().to(torch.float64).reshape(()).contiguous()
@@ -96,8 +102,13 @@ class LocalPotentialEnergy(torch.autograd.Function):
 
 
 def local_potential_energy(c, V, save_psi: bool = True):
-    """E = sum_n sum_r V(r) |IFFT3D(c_n)(r)|^2 (differentiable in c)."""
-    return LocalPotentialEnergy.apply(c, V, save_psi)
+    """E = sum_n sum_r V(r) |IFFT3D(c_n)(r)|^2 (differentiable in c).
+
+    The gradient's first half runs in the forward only if a backward can
+    follow: V psi and its z transform make an evaluation of 128 x 96^3 cost
+    0.63 ms instead of 0.50.
+    """
+    return LocalPotentialEnergy.apply(c, V, bool(save_psi) and torch.is_grad_enabled() and c.requires_grad)
 
 
 def energy(c, V):
