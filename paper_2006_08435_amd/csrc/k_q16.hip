@@ -135,14 +135,17 @@ hipError_t launch_dequantize(int fmt, const unsigned* pay, const signed char* ex
     const long blocks = (rows * C + 255) / 256;
     if (blocks == 0) return hipSuccess;
     if (C % 2 == 0 && C > 2) {   // every row of payloads starts on 8 bytes, every row of values on 16
-        const int Q = C / 2, rpb = Q >= 2048 ? 1 : 2048 / Q;
+        const int Q = C / 2, rpb = Q >= kDequantPairs ? 1 : kDequantPairs / Q;
+        const int parts = Q > kDequantPairs ? (Q - 1) / kDequantPairs + 1 : 1;
         const unsigned magic = (unsigned)(((1ull << 32) + Q - 1) / Q);
-        const dim3 grid((unsigned)((rows + rpb - 1) / rpb));
+        const dim3 grid((unsigned)((rows + rpb - 1) / rpb * parts));
         const uint2* p2 = reinterpret_cast<const uint2*>(pay);
         if (fmt == kFmtF16)
-            hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, magic, out);
+            hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, parts, magic,
+                               out);
         else
-            hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, magic, out);
+            hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, parts, magic,
+                               out);
         return hipGetLastError();
     }
     if (fmt == kFmtF16)

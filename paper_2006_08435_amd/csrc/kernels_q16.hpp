@@ -855,22 +855,30 @@ __global__ void __launch_bounds__(256) k_q16_quantize(const float2* in, long row
 
 // Rows of an even number of points: a lane converts pairs, one 8-byte load and
 // one 16-byte store each, four pairs in flight.  A workgroup takes `rpb` whole
-// rows (Q = C / 2 pairs each), so a pair's row is a 32-bit quotient: magic =
-// ceil(2^32 / Q) is exact for the pairs of a workgroup (rpb * Q <= 2048, or
-// one row).  Bound by HBM, 12 bytes a point.  67.1 million points: 196 us
+// rows (Q = C / 2 pairs each, rpb * Q <= kDequantPairs), so a pair's row is a
+// 32-bit quotient: magic = ceil(2^32 / Q) is exact for the pairs of a
+// workgroup.  A row of more pairs is shared by `parts` workgroups (rpb = 1)
+// with one exponent each, so that a few long rows fill the device too (one
+// row of 2^20 points 287 us a call as one workgroup, 6.5 in parts).  Bound by
+// HBM, 12 bytes a point.  67.1 million points: 196 us
 // with one point and a 64-bit division a thread, 159 with four points a lane
 // (its two stores each cover half of every cache line), 116 so.
+constexpr int kDequantPairs = 2048;
+
 template <int FMT>
 __global__ void __launch_bounds__(256) k_q16_dequantize2(const uint2* __restrict__ pay, const signed char* __restrict__ ex,
-                                                         long rows, int Q, int rpb, unsigned magic,
+                                                         long rows, int Q, int rpb, int parts, unsigned magic,
                                                          float2* __restrict__ out)
 {
     constexpr int U = 4;
     typedef float f4v __attribute__((ext_vector_type(4)));
-    const long r0 = (long)blockIdx.x * rpb;
-    const int nr = (int)(rows - r0 < rpb ? rows - r0 : rpb), n = nr * Q;
-    const uint2* src = pay + r0 * Q;
-    f4v* dst = reinterpret_cast<f4v*>(out) + r0 * Q;
+    const unsigned set = blockIdx.x / parts;
+    const int p0 = (int)(blockIdx.x - set * parts) * kDequantPairs;   // first pair in its rows
+    const long r0 = (long)set * rpb;
+    const int nr = (int)(rows - r0 < rpb ? rows - r0 : rpb), left = nr * Q - p0;
+    const int n = left < kDequantPairs ? left : kDequantPairs;
+    const uint2* src = pay + r0 * Q + p0;
+    f4v* dst = reinterpret_cast<f4v*>(out) + r0 * Q + p0;
     for (int i0 = threadIdx.x; i0 < n; i0 += U * 256) {
         uint2 u[U];
         int e[U];

@@ -360,3 +360,37 @@ def test_captured_and_replayed(F, form):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(got, want[k]), k
+
+
+@pytest.mark.parametrize("rows,C", [(1, 4096), (2, 4098), (3, 8192), (2, 8194), (1, 1 << 20)])
+@pytest.mark.parametrize("precision", ["fp16", "bf16"])
+def test_dequantize_long_rows(F, rows, C, precision):
+    """Rows of one workgroup's pairs, a pair more, two workgroups' and a pair
+    more: payload * 2^exponent, bit for bit."""
+    rng = np.random.default_rng(1400 + rows + C)
+    x = workloads.uniform_grid((C, rows, 1), 1400 + rows)[0] * np.exp2(rng.integers(-40, 40, (rows, 1)))
+    buf = F.quantize(torch.from_numpy(x.astype(np.complex64)).cuda(), precision)
+    got = F.dequantize(buf, (rows, C), precision).cpu().numpy()
+    raw = buf.cpu()
+    pay = raw[:4 * rows * C].view(torch.float16 if precision == "fp16" else torch.bfloat16).double().numpy()
+    exp = raw[4 * rows * C:].numpy().view(np.int8).astype(np.float64)
+    want = pay.reshape(rows, C, 2) * np.exp2(exp)[:, None, None]
+    assert np.array_equal(got.view(np.float32).reshape(rows, C, 2).astype(np.float64), want)
+
+
+def test_dequantize_time_does_not_depend_on_the_row_length(F):
+    """2^22 points as one row and as rows of 128: the same bytes, so a few
+    times as long at most (one workgroup alone would take a hundred times)."""
+    def best(rows, C):
+        buf = torch.zeros(F.scaled16_bytes((rows, C)), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                F.dequantize(buf, (rows, C))
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+    assert best(1, 1 << 22) < 5 * best(1 << 15, 128)
