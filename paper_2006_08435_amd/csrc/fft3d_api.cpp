@@ -188,6 +188,7 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
     const bool split = large && nx == ny && ny == nz && split_batch_ok(nx, batch);
     if (split) {
         p->tw_n1 = append(nx / split_parts_of(nx), direction, 0);
+        p->tw_cols = append(ny, direction, 4);
         p->tw_rt = (long)tab.size();
         for (int m = 0; m < nx; ++m) {
             const double a = 2.0 * M_PI * (double)m / (double)nx;
@@ -292,6 +293,9 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
         const int cus = device_cus(dev);
         p->passes.push_back({Pass::kSplitPlaneK, nx, B * nz, {}, p->tw_x, cus});
         p->passes.push_back({Pass::kSplitZK, nx, B, {}, p->tw_z, cus});
+        p->inplace_passes.push_back({Pass::kRowK, nx, B * nz * ny, {}, p->tw_x});
+        p->inplace_passes.push_back({Pass::kSplitColK, ny, 0, ymap, p->tw_cols});
+        p->inplace_passes.push_back({Pass::kStrK, nz, 0, zmap, p->tw_z});
     } else if (rect_init(nx, ny, B * nz, direction)) {
         // the plane in LDS, as one pass (nx != ny, or a larger nz)
         p->passes.push_back({Pass::kRectK, nx, B * nz, {}, p->tw_x});
@@ -430,6 +434,7 @@ static hipError_t run_pass(const fft3d_plan_s* p, const Pass& ps, const float2* 
         return split_plane_fn(ps.n, S)(src, dst, tw, p->d_tw + p->tw_n1, ps.count, ps.grid, st);
     case Pass::kSplitZK:
         return split_z_fn(ps.n, S)(src, dst, tw, p->d_tw + p->tw_rt, ps.count, ps.grid, st);
+    case Pass::kSplitColK: return split_cols_fn(ps.n, S)(src, dst, tw, ps.map, st);
     case Pass::kRectK:
         return launch_plane_rect(src, dst, p->d_tw + p->tw_x, p->d_tw + p->tw_y, p->nx, p->ny, ps.count, S, st);
     case Pass::kPlaneK: return plane_fn(ps.n, S)(src, dst, tw, ps.count, st);
@@ -495,8 +500,9 @@ int fft3d_exec(fft3d_plan_t p, const void* in, void* out, fft3d_stream_t stream)
         }
         return FFT3D_OK;
     }
-    for (size_t i = 0; i < p->passes.size() && e == hipSuccess; ++i)
-        e = run_pass(p, p->passes[i], i == 0 ? src : dst, dst, st);
+    const std::vector<Pass>& passes = src == dst && !p->inplace_passes.empty() ? p->inplace_passes : p->passes;
+    for (size_t i = 0; i < passes.size() && e == hipSuccess; ++i)
+        e = run_pass(p, passes[i], i == 0 ? src : dst, dst, st);
     if (e == hipSuccess && p->passes.empty() && src != dst)
         e = hipMemcpyAsync(dst, src, fft3d_buffer_bytes(p), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) {

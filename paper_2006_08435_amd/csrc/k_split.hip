@@ -9,7 +9,7 @@ static hipError_t launch_split_plane(const float2* in, float2* out, const float2
                                      int cus, hipStream_t st)
 {
     using G = SplitGeom<N>;
-    if (in == out) {   // the rows move: whole columns instead
+    if (in == out) {   // this pass alone: its rows move, so whole columns instead
         hipError_t e = axis_row_fn(N, S)(in, out, tw_x, planes * N, st);
         if (e == hipSuccess) {
             constexpr int XT = (N + 15) / 16;
@@ -38,12 +38,25 @@ static hipError_t launch_split_z(const float2* in, float2* out, const float2* tw
     return hipGetLastError();
 }
 
+template <int N, int S>
+static hipError_t launch_split_cols(const float2* in, float2* out, const float2* tw, const AxisMap& m, hipStream_t st)
+{
+    constexpr int L = 32;   // as the strided passes of these lengths (k_axis_large.hip)
+    const long blocks = (m.lines + L - 1) / L;
+    hipLaunchKernelGGL((k_axis_str<N, S, L, false, 0, 4>), dim3((unsigned)blocks), dim3(AxisGeom<N, L, 4>::T), 0, st,
+                       in, out, tw, in_runs(m, blocks, L, false), nullptr, nullptr, 0L, 0.0, nullptr, 0L);
+    return hipGetLastError();
+}
+
 #define FFT3D_SPLIT_PLANE_CASE(n)                                              \
     case n:                                                                    \
         return sign < 0 ? &launch_split_plane<n, -1> : &launch_split_plane<n, 1>;
 #define FFT3D_SPLIT_Z_CASE(n)                                                  \
     case n:                                                                    \
         return sign < 0 ? &launch_split_z<n, -1> : &launch_split_z<n, 1>;
+#define FFT3D_SPLIT_COLS_CASE(n)                                               \
+    case n:                                                                    \
+        return sign < 0 ? &launch_split_cols<n, -1> : &launch_split_cols<n, 1>;
 #define FFT3D_SPLIT_PARTS_CASE(n)                                              \
     case n:                                                                    \
         return SplitGeom<n>::R;
@@ -60,6 +73,14 @@ SplitZFn split_z_fn(int n, int sign)
 {
     switch (n) {
         FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_Z_CASE)
+    default: return nullptr;
+    }
+}
+
+AxisVarFn split_cols_fn(int n, int sign)
+{
+    switch (n) {
+        FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_COLS_CASE)
     default: return nullptr;
     }
 }

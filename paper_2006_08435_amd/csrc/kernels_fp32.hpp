@@ -1171,11 +1171,13 @@ inline AxisMap in_runs(AxisMap m, long tiles, int L, bool with_V)
     return m;
 }
 
-template <int N, int L>
+// K: the schedule kind whose radices the threads are counted for (the tuner's
+// alternative orders run with the default's).
+template <int N, int L, int K = 0>
 struct AxisGeom {
     static constexpr int LP = odd_stride(L);
     static constexpr int WORDS = N * LP;
-    static constexpr int T = threads_for<N>(L);
+    static constexpr int T = threads_for_kind<N, K == 4 ? 4 : 0>(L);
     static_assert(T % L == 0 || L % T == 0, "tile lines and threads must nest");
 };
 
@@ -1301,13 +1303,13 @@ __device__ __forceinline__ long z_tile(const AxisMap& m)
 // K: schedule kind (dense form only: 0 default, 2 the tuner's alternative
 // order, with a twiddle table of the same kind).
 template <int N, int S, int L, bool ENERGY = false, int PRUNE = 0, int K = 0>
-__global__ void __launch_bounds__((AxisGeom<N, L>::T))
+__global__ void __launch_bounds__((AxisGeom<N, L, K>::T))
 k_axis_str(const float2* in, float2* out, const float2* __restrict__ tw, AxisMap m, const float* __restrict__ V,
            double* __restrict__ partials, long vol, double R2 = 0.0, const SphereRow* __restrict__ rows = nullptr,
            long npts = 0)
 {
     static_assert(K == 0 || (!ENERGY && PRUNE == 0), "schedule kinds other than 0 serve the dense form only");
-    using G = AxisGeom<N, L>;
+    using G = AxisGeom<N, L, K>;
     using P = Plan1D<N, K>;
     constexpr int T = G::T;
     static_assert(T % L == 0, "each thread keeps one line");

@@ -10,8 +10,15 @@
 // of every plane, L points of x at a time: twiddle and R-point DFT across y0 in
 // registers (the factors are the same for the whole tile), then the z lines in
 // LDS, stored to the rows k1 + N1 k2.  Its tile reads and writes the same
-// points, so it runs in place; pass one moves rows, so with in == out
-// k_axis_row and k_split_y (whole columns in LDS) produce its result instead.
+// points, so it runs in place; pass one moves rows, so a transform with in ==
+// out takes three passes: rows, whole y columns with the same butterflies
+// (k_axis_str of schedule kind 4), and the plain z pass.  They leave the same
+// bits.  Whole columns also serve a caller who runs pass one alone in place
+// (k_split_y).  In place, copy of the input included, us, the three passes with
+// default radices -> these: 16 x 150^3 670 -> 623, 8 x 162^3 417 -> 375,
+// 12 x 160^3 557 -> 557, 4 x 256^3 761 -> 763, one 256^3 166.1 -> 168.5, one
+// 144^3 38.0 -> 38.9 (a third stage along y), one 135^3 44.1 -> 40.0; rows,
+// k_split_y and k_split_z instead: 794, 500, 588, 820, 173.5, 43.6, 50.1.
 // Both passes hold one tile of up to 16384 points a compute unit, bound by HBM
 // and their barriers as k_plane_pf is.  Inverse + forward in us, three passes
 // -> two: 4 x 256^3 1161 -> 776 (322 at the copy rate for one sweep each way),
@@ -23,25 +30,6 @@
 #include "kernels_fp32.hpp"
 
 namespace fft3d {
-
-// Points of x a z tile for R parts: 32 (256 bytes a run) where that tile then
-// has at most 13000 points, else 16.
-constexpr int split_lines(int n, int r) { return 32 * r * n <= 13000 ? 32 : 16; }
-constexpr bool split_z_fits(int n, int r) { return split_lines(n, r) * r * n <= 18432; }
-
-// The parts R of a plane: the fewest whose tile has at most 12300 points, so
-// that its next rows (12 points a thread) stay in registers beside two turns
-// of a radix-10 stage; where the z tile would not fit then, the fewest with at
-// most 16384 points (240; 256, whose stages are whole turns).
-constexpr int split_parts(int n)
-{
-    for (int r = 2; r <= 5; ++r)
-        if (n % r == 0 && n / r * n <= 12300 && split_z_fits(n, r)) return r;
-    for (int r = 2; r <= 5; ++r)
-        if (n % r == 0 && n / r * n <= 16384 && split_z_fits(n, r)) return r;
-    return 0;
-}
-constexpr bool split_ok(int n) { return n > 128 && n <= 256 && split_parts(n) > 0; }
 
 #define FFT3D_FOR_EACH_SPLIT_SIZE(X)                                           \
     X(135) X(144) X(150) X(160) X(162) X(180) X(192) X(200) X(216) X(240)      \
@@ -153,8 +141,9 @@ k_split_plane(const float2* in, float2* out, const float2* __restrict__ tw_x, co
     }
 }
 
-// The length-N1 transforms of pass one on whole columns, in place: the rows
-// already transformed along x.  A workgroup takes L adjacent columns of a plane.
+// The length-N1 transforms of pass one on whole columns, for pass one run
+// alone in place: the rows already transformed along x.  A workgroup takes L
+// adjacent columns of a plane.
 template <int N, int S>
 __global__ void __launch_bounds__(SplitGeom<N>::T)
 k_split_y(float2* buf, const float2* __restrict__ tw_y)

@@ -28,7 +28,7 @@ int twiddles_into(float2* t, int cap, int n, int sign, int kind = 0);
 // every later pass works in place on the output buffer.
 struct Pass {
     enum Kind { kCubeK, kPlaneK, kPlanePfK, kRowK, kStrK, kFusedK, kQ16PlaneK, kQ16SlabK, kPlanePrunedK, kStrPrunedK, kRealK,
-                kCubeLinesK, kRectK, kSplitPlaneK, kSplitZK } kind;
+                kCubeLinesK, kRectK, kSplitPlaneK, kSplitZK, kSplitColK } kind;
     int n;        // transform length of this pass
     long count;   // grids / planes / rows (cube, plane, row kinds)
     AxisMap map;  // strided kind
@@ -95,10 +95,12 @@ struct fft3d_plan_s {
     fft3d::SphereRow* d_rows;  // packed-sphere row table [nz][ny] (device)
     long sphere_pts;           // points per grid inside the cutoff sphere
     std::vector<fft3d::Pass> dense_passes;   // schedule without the cutoff
+    std::vector<fft3d::Pass> inplace_passes; // split form: the passes of an exec with in == out
     bool real;                 // plan from fft3d_plan_real (r2c forward / c2r inverse)
     long tw_rt;                // real plans: offset of the split/merge roots W_N^{direction*k}, k <= N/4;
                                // split form: of the roots W_N^{direction*k}, k < N
     long tw_n1;                // split form: offset of the length N / parts table
+    long tw_cols;              // split form: offset of the table of schedule kind 4
     bool many;                 // plan from fft3d_plan_many
     fft3d::ManyPlan mp;
 };

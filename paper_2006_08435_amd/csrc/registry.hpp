@@ -143,6 +143,10 @@ using SplitPlaneFn = hipError_t (*)(const float2* in, float2* out, const float2*
 using SplitZFn = hipError_t (*)(const float2* in, float2* out, const float2* tw_z, const float2* root, long grids,
                                 int cus, hipStream_t st);
 SplitPlaneFn split_plane_fn(int n, int sign);
+// Whole y columns by the two-pass form's butterflies (schedule kind 4), a
+// strided pass: in place, rows, these columns and the plain z pass leave the
+// values that the two passes leave.
+AxisVarFn split_cols_fn(int n, int sign);
 SplitZFn split_z_fn(int n, int sign);
 int split_parts_of(int n);
 bool split_batch_ok(int n, int batch);

@@ -165,12 +165,45 @@ __host__ __device__ constexpr Sched make_sched_rev(int n)
     return s;
 }
 
+// Two-pass form of cubic grids above 128 points a side (kernels_split.hpp).
+// Points of x a z tile for R parts: 32 (256 bytes a run) where that tile then
+// has at most 13000 points, else 16.
+__host__ __device__ constexpr int split_lines(int n, int r) { return 32 * r * n <= 13000 ? 32 : 16; }
+__host__ __device__ constexpr bool split_z_fits(int n, int r) { return split_lines(n, r) * r * n <= 18432; }
+
+// The parts R of a plane: the fewest whose tile has at most 12300 points, so
+// that its next rows (12 points a thread) stay in registers beside two turns
+// of a radix-10 stage; where the z tile would not fit then, the fewest with at
+// most 16384 points (240; 256, whose stages are whole turns).
+__host__ __device__ constexpr int split_parts(int n)
+{
+    for (int r = 2; r <= 5; ++r)
+        if (n % r == 0 && n / r * n <= 12300 && split_z_fits(n, r)) return r;
+    for (int r = 2; r <= 5; ++r)
+        if (n % r == 0 && n / r * n <= 16384 && split_z_fits(n, r)) return r;
+    return 0;
+}
+__host__ __device__ constexpr bool split_ok(int n) { return n > 128 && n <= 256 && split_parts(n) > 0; }
+
+// The length as that form computes it along y (kind 4): its parts' transforms
+// by their default schedule, then one butterfly across the parts.
+__host__ __device__ constexpr Sched make_sched_split(int n)
+{
+    const int r = split_parts(n);
+    if (r == 0) return make_sched(n);
+    Sched s = make_sched(n / r);
+    s.r[s.count++] = r;
+    return s;
+}
+
 // kind 0: default; 1: radix 16 first (reduced-precision form); 2: the
-// autotuner's alternative order; 3: the default order reversed.
+// autotuner's alternative order; 3: the default order reversed; 4: parts and
+// the butterfly across them (lengths of the two-pass form above 128).
 __host__ __device__ constexpr Sched make_sched_kind(int n, int kind)
 {
     return kind == 1 ? make_sched16(n)
-                     : (kind == 2 ? make_sched_alt(n) : (kind == 3 ? make_sched_rev(n) : make_sched(n)));
+                     : (kind == 2 ? make_sched_alt(n)
+                                  : (kind == 3 ? make_sched_rev(n) : (kind == 4 ? make_sched_split(n) : make_sched(n))));
 }
 
 __host__ __device__ constexpr int sched_ns(const Sched& s, int stage)

@@ -394,3 +394,18 @@ def test_dequantize_time_does_not_depend_on_the_row_length(F):
             times.append(start.elapsed_time(end))
         return min(times)
     assert best(1, 1 << 22) < 5 * best(1 << 15, 128)
+
+
+@pytest.mark.parametrize("n,b", [(135, 2), (144, 1), (150, 1), (160, 1), (162, 1), (180, 1), (192, 1), (200, 1), (216, 1),
+                                 (240, 3), (256, 1)])
+@pytest.mark.parametrize("sign", [INVERSE, FORWARD])
+def test_in_place_above_128(F, n, b, sign):
+    """In place a plan of the two-pass form takes three passes of other
+    kernels with the same butterflies: the same bits."""
+    gen = torch.Generator(device="cuda").manual_seed(n + 1)
+    x = torch.view_as_complex(torch.rand((b, n, n, n, 2), generator=gen, device="cuda") - 0.5)
+    plan = F.Plan(n, n, n, b, "fp32", sign)
+    assert "k_split_plane,k_split_z" in plan.describe()
+    y = plan.exec(x)
+    plan.exec(x, x)
+    assert torch.equal(x, y)
