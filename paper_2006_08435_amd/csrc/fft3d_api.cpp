@@ -133,8 +133,8 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
     const bool large = nx > 128 || ny > 128 || nz > 128;
     if (large && precision != FFT3D_FP32) { set_error(FFT3D_E_UNSUPPORTED); return nullptr; }
     const long vol = (long)nx * ny * nz;
-    // 2^36 points (512 GiB of complex64) bounds every grid dimension of every
-    // launch below 2^31 workgroups.
+    // 2^36 points (512 GiB of complex64) bounds every count of workgroups, planes
+    // or tiles below 2^31.
     if ((long)batch * vol > (1L << 36)) { set_error(FFT3D_E_INVALID_ARG); return nullptr; }
     const bool q16 = precision != FFT3D_FP32;
     if (q16 && (nx != ny || ny != nz || !q16_plane_fn(nx, direction))) { set_error(FFT3D_E_UNSUPPORTED); return nullptr; }

@@ -40,21 +40,18 @@ static hipError_t launch_axis_str(const float2* in, float2* out, const float2* t
                                   const float* V, double* partials, long vol, hipStream_t st)
 {
     const long blocks = axis_str_blocks(m.lines);
-    if (energy == 2) {
-        hipLaunchKernelGGL((k_axis_energy<N, S, kAxisLines>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, tw, in_runs(m, blocks, kAxisLines, true), V,
-                           partials, vol);
-        return hipGetLastError();
-    }
-    if (energy)
-        hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, true>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw,
-                           in_runs(m, blocks, kAxisLines, true), V, partials, vol, 0.0);
-    else
-        hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false>), dim3((unsigned)blocks),
-                           dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw,
-                           in_runs(m, blocks, kAxisLines, false), V, partials, vol, 0.0);
-    return hipGetLastError();
+    constexpr int T = AxisGeom<N, kAxisLines>::T;
+    return launch_tiles(in_runs(m, blocks, kAxisLines, energy != 0), blocks, [&](const AxisMap& map, unsigned grid) {
+        if (energy == 2)
+            hipLaunchKernelGGL((k_axis_energy<N, S, kAxisLines>), dim3(grid), dim3(T), 0, st, in, tw, map, V, partials,
+                               vol);
+        else if (energy)
+            hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, true>), dim3(grid), dim3(T), 0, st, in, out, tw, map, V,
+                               partials, vol, 0.0);
+        else
+            hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false>), dim3(grid), dim3(T), 0, st, in, out, tw, map, V,
+                               partials, vol, 0.0);
+    });
 }
 
 template <int N, int S>
@@ -62,22 +59,21 @@ static hipError_t launch_axis_str_pruned(const float2* in, float2* out, const fl
                                          double R2, const SphereRow* rows, long npts, hipStream_t st)
 {
     const long blocks = axis_str_blocks(map.lines);
-    const AxisMap m = in_runs(map, blocks, kAxisLines, false);
+    constexpr int T = AxisGeom<N, kAxisLines>::T;
+    if (S > 0 && rows) return hipErrorInvalidValue;
     // inverse plans prune the loads (sphere-limited input), forward plans
     // lines and stores (optionally scattering into a packed sphere)
-    if constexpr (S < 0) {
-        if (rows) {
-            hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, 3>), dim3((unsigned)blocks),
-                               dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw, m, nullptr, nullptr, 0L, R2, rows,
-                               npts);
-            return hipGetLastError();
+    return launch_tiles(in_runs(map, blocks, kAxisLines, false), blocks, [&](const AxisMap& m, unsigned grid) {
+        if constexpr (S < 0) {
+            if (rows) {
+                hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, 3>), dim3(grid), dim3(T), 0, st, in, out, tw, m,
+                                   nullptr, nullptr, 0L, R2, rows, npts);
+                return;
+            }
         }
-    } else {
-        if (rows) return hipErrorInvalidValue;
-    }
-    hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, (S > 0 ? 1 : 2)>), dim3((unsigned)blocks),
-                       dim3(AxisGeom<N, kAxisLines>::T), 0, st, in, out, tw, m, nullptr, nullptr, 0L, R2, nullptr, 0L);
-    return hipGetLastError();
+        hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, (S > 0 ? 1 : 2)>), dim3(grid), dim3(T), 0, st, in, out,
+                           tw, m, nullptr, nullptr, 0L, R2, nullptr, 0L);
+    });
 }
 
 #define FFT3D_STR_PRUNED_CASE(n)                                               \
@@ -99,14 +95,15 @@ static hipError_t launch_hloc(float2* buf, const float2* tw_inv, const float2* t
 {
     const long blocks = axis_str_blocks(map.lines);
     // the pruned form gains from whole cache lines only (64 x 80^3 249 us, in runs 251)
-    const AxisMap m = in_runs(map, blocks, kAxisLines, mode == 0);
-    if (mode)
-        hipLaunchKernelGGL((k_axis_hloc<N, kAxisLines, 1>), dim3((unsigned)blocks), dim3(AxisGeom<N, kAxisLines>::T),
-                           0, st, buf, tw_inv, tw_fwd, m, V, scale, mult, partials, vol, R2);
-    else
-        hipLaunchKernelGGL((k_axis_hloc<N, kAxisLines, 0>), dim3((unsigned)blocks), dim3(AxisGeom<N, kAxisLines>::T),
-                           0, st, buf, tw_inv, tw_fwd, m, V, scale, mult, partials, vol, R2);
-    return hipGetLastError();
+    constexpr int T = AxisGeom<N, kAxisLines>::T;
+    return launch_tiles(in_runs(map, blocks, kAxisLines, mode == 0), blocks, [&](const AxisMap& m, unsigned grid) {
+        if (mode)
+            hipLaunchKernelGGL((k_axis_hloc<N, kAxisLines, 1>), dim3(grid), dim3(T), 0, st, buf, tw_inv, tw_fwd, m, V,
+                               scale, mult, partials, vol, R2);
+        else
+            hipLaunchKernelGGL((k_axis_hloc<N, kAxisLines, 0>), dim3(grid), dim3(T), 0, st, buf, tw_inv, tw_fwd, m, V,
+                               scale, mult, partials, vol, R2);
+    });
 }
 
 #define FFT3D_HLOC_CASE(n)                                                     \

@@ -28,9 +28,10 @@ static hipError_t launch_str_large(const float2* in, float2* out, const float2* 
     if (energy) return hipErrorInvalidValue;   // the energy form is provided up to 128 only
     constexpr int L = large_lines<N>();
     const long blocks = (m.lines + L - 1) / L;
-    hipLaunchKernelGGL((k_axis_str<N, S, L, false>), dim3((unsigned)blocks), dim3(AxisGeom<N, L>::T), 0, st, in, out,
-                       tw, in_runs(m, blocks, L, false), nullptr, nullptr, 0L, 0.0, nullptr, 0L);
-    return hipGetLastError();
+    return launch_tiles(in_runs(m, blocks, L, false), blocks, [&](const AxisMap& map, unsigned grid) {
+        hipLaunchKernelGGL((k_axis_str<N, S, L, false>), dim3(grid), dim3(AxisGeom<N, L>::T), 0, st, in, out, tw, map,
+                           nullptr, nullptr, 0L, 0.0, nullptr, 0L);
+    });
 }
 
 template <int N, int S>

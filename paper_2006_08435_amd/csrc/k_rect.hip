@@ -57,7 +57,7 @@ hipError_t launch_plane_rect(const float2* in, float2* out, const float2* tw_x, 
     const RectArgs a{in,         out,       tw_x,      tw_y,     sched_tw_len(make_sched(nx)),
                      sched_tw_len(make_sched(ny)),     planes,   nx,   ny,   rect_tile(nx, ny),
                      magic(nx),  magic(ny), nx % 2 ? magic(nx) : (nx > 2 ? magic(nx / 2) : 0u)};
-    const unsigned grid = (unsigned)(planes < (1L << 24) ? planes : (1L << 24));
+    const unsigned grid = (unsigned)(planes < kMaxBlocks ? planes : kMaxBlocks);
     return (sign < 0 ? rect_fwd : rect_inv)(rect_class(nx, ny), a, grid, (size_t)rect_lds_bytes(nx, ny), st);
 }
 

@@ -12,8 +12,9 @@ static hipError_t launch_split_plane(const float2* in, float2* out, const float2
     if (in == out) {   // this pass alone: its rows move, so whole columns instead
         hipError_t e = axis_row_fn(N, S)(in, out, tw_x, planes * N, st);
         if (e == hipSuccess) {
-            constexpr int XT = (N + 15) / 16;
-            hipLaunchKernelGGL((k_split_y<N, S>), dim3((unsigned)(planes * XT)), dim3(G::T), 0, st, out, tw_y);
+            const long tiles = planes * split_y_tiles(N);
+            hipLaunchKernelGGL((k_split_y<N, S>), dim3((unsigned)(tiles < kMaxBlocks ? tiles : kMaxBlocks)), dim3(G::T),
+                               0, st, out, tw_y, tiles);
             e = hipGetLastError();
         }
         return e;
@@ -43,9 +44,10 @@ static hipError_t launch_split_cols(const float2* in, float2* out, const float2*
 {
     constexpr int L = 32;   // as the strided passes of these lengths (k_axis_large.hip)
     const long blocks = (m.lines + L - 1) / L;
-    hipLaunchKernelGGL((k_axis_str<N, S, L, false, 0, 4>), dim3((unsigned)blocks), dim3(AxisGeom<N, L, 4>::T), 0, st,
-                       in, out, tw, in_runs(m, blocks, L, false), nullptr, nullptr, 0L, 0.0, nullptr, 0L);
-    return hipGetLastError();
+    return launch_tiles(in_runs(m, blocks, L, false), blocks, [&](const AxisMap& map, unsigned grid) {
+        hipLaunchKernelGGL((k_axis_str<N, S, L, false, 0, 4>), dim3(grid), dim3(AxisGeom<N, L, 4>::T), 0, st, in, out,
+                           tw, map, nullptr, nullptr, 0L, 0.0, nullptr, 0L);
+    });
 }
 
 #define FFT3D_SPLIT_PLANE_CASE(n)                                              \

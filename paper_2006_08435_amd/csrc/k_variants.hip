@@ -28,9 +28,10 @@ template <int N, int S, int K, int L>
 static hipError_t launch_axis_v(const float2* in, float2* out, const float2* tw, const AxisMap& m, hipStream_t st)
 {
     const long blocks = (m.lines + L - 1) / L;
-    hipLaunchKernelGGL((k_axis_str<N, S, L, false, 0, K>), dim3((unsigned)blocks), dim3(AxisGeom<N, L>::T), 0, st, in,
-                       out, tw, in_runs(m, blocks, L, false), nullptr, nullptr, 0L, 0.0, nullptr, 0L);
-    return hipGetLastError();
+    return launch_tiles(in_runs(m, blocks, L, false), blocks, [&](const AxisMap& map, unsigned grid) {
+        hipLaunchKernelGGL((k_axis_str<N, S, L, false, 0, K>), dim3(grid), dim3(AxisGeom<N, L>::T), 0, st, in, out, tw,
+                           map, nullptr, nullptr, 0L, 0.0, nullptr, 0L);
+    });
 }
 
 #define FFT3D_PLANE_V_CASE(n)                                                  \

@@ -1149,6 +1149,7 @@ struct AxisMap {
     int odiv;
     long shi, slo, es;
     int run = 0;     // tiles of an XCD's run (z_tile), 0: launch order
+    unsigned first = 0;   // first tile of this launch (launch_tiles)
 };
 
 // The map of a strided pass of `tiles` tiles of L lines with its order of
@@ -1169,6 +1170,28 @@ inline AxisMap in_runs(AxisMap m, long tiles, int L, bool with_V)
     const bool gains = m.es % 16 != 0 || (with_V && lines % (8 * L) != 0);
     m.run = gains && tiles >= 512 && lines >= 4 * L ? (int)((lines + 4 * L) / (8 * L)) : 0;
     return m;
+}
+
+// Workgroups of one launch: HIP takes fewer than 2^32 work items in a
+// dimension, and a workgroup has at most 1024.  Grids of more go round a loop
+// in the kernel or take several launches (launch_tiles).
+constexpr long kMaxBlocks = 1L << 21;
+static_assert(kMaxBlocks * 1024 < (1L << 32), "below HIP's limit");
+
+// Launches a strided pass of `tiles` tiles: f(map, workgroups), more than once
+// only for grids beyond kMaxBlocks, the last tiles first as in z_tile.
+template <class F>
+inline hipError_t launch_tiles(AxisMap m, long tiles, F&& f)
+{
+    hipError_t e = hipSuccess;
+    for (long end = tiles; end > 0 && e == hipSuccess;) {
+        const long n = end < kMaxBlocks ? end : kMaxBlocks;
+        end -= n;
+        m.first = (unsigned)end;
+        f(m, (unsigned)n);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // K: the schedule kind whose radices the threads are counted for (the tuner's
@@ -1288,9 +1311,9 @@ __device__ __forceinline__ long rev_tile() { return (long)(gridDim.x - 1 - block
 __device__ __forceinline__ long z_tile(const AxisMap& m)
 {
     const unsigned b = gridDim.x - 1 - blockIdx.x;
-    if (__builtin_expect(m.run == 0, 1)) return b;
+    if (__builtin_expect(m.run == 0, 1)) return m.first + b;
     const unsigned run = (unsigned)m.run, group = 8 * run, g0 = b / group * group, r = b - g0;
-    return g0 + group > gridDim.x ? b : g0 + r % 8 * run + r / 8;
+    return m.first + (g0 + group > gridDim.x ? b : g0 + r % 8 * run + r / 8);
 }
 
 // ENERGY: the pass is the last one of an inverse transform psi = IFFT(c);

@@ -144,35 +144,41 @@ k_split_plane(const float2* in, float2* out, const float2* __restrict__ tw_x, co
 // The length-N1 transforms of pass one on whole columns, for pass one run
 // alone in place: the rows already transformed along x.  A workgroup takes L
 // adjacent columns of a plane.
+constexpr int kSplitYLines = 16;
+constexpr int split_y_tiles(int n) { return (n + kSplitYLines - 1) / kSplitYLines; }   // of a plane
+
 template <int N, int S>
 __global__ void __launch_bounds__(SplitGeom<N>::T)
-k_split_y(float2* buf, const float2* __restrict__ tw_y)
+k_split_y(float2* buf, const float2* __restrict__ tw_y, long tiles)
 {
     using G = SplitGeom<N>;
-    constexpr int R = G::R, N1 = G::N1, T = G::T, L = 16, LP = odd_stride(L), XT = (N + L - 1) / L;
+    constexpr int R = G::R, N1 = G::N1, T = G::T, L = kSplitYLines, LP = odd_stride(L), XT = split_y_tiles(N);
     __shared__ float2 lds[N * LP];
     const int tid = threadIdx.x;
-    const long p = blockIdx.x / XT;
-    const int x0 = (int)(blockIdx.x - p * XT) * L;
-    float2* plane = buf + p * (N * N) + x0;
-    for (int i = tid; i < N * L; i += T) {
-        const int y = i / L, x = i - y * L;
-        lds[y * LP + x] = x0 + x < N ? plane[(long)y * N + x] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    // line (y0, x): element y1 is the tile's row y0 + R y1, the result row N1 y0 + k1
-    struct Out {
-        float2* p;
-        int valid;
-        __device__ __forceinline__ void store(int line, int e, float2 v) const
-        {
-            const int y0 = line / L, x = line - y0 * L;
-            if (x < valid) p[(long)(N1 * y0 + e) * N + x] = v;
+    for (long t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const long p = t / XT;
+        const int x0 = (int)(t - p * XT) * L;
+        float2* plane = buf + p * (N * N) + x0;
+        for (int i = tid; i < N * L; i += T) {
+            const int y = i / L, x = i - y * L;
+            lds[y * LP + x] = x0 + x < N ? plane[(long)y * N + x] : make_float2(0.f, 0.f);
         }
-    };
-    const LdsAcc2<L, LP, 1, R * LP> a{lds};
-    const Out o{plane, N - x0};
-    run_tail<N1, S, R * L, T, 0, false>(a, o, tw_y, tid);
+        __syncthreads();
+        // line (y0, x): element y1 is the tile's row y0 + R y1, the result row N1 y0 + k1
+        struct Out {
+            float2* p;
+            int valid;
+            __device__ __forceinline__ void store(int line, int e, float2 v) const
+            {
+                const int y0 = line / L, x = line - y0 * L;
+                if (x < valid) p[(long)(N1 * y0 + e) * N + x] = v;
+            }
+        };
+        const LdsAcc2<L, LP, 1, R * LP> a{lds};
+        const Out o{plane, N - x0};
+        run_tail<N1, S, R * L, T, 0, false>(a, o, tw_y, tid);
+        __syncthreads();   // the tile is free for the next one
+    }
 }
 
 // Pass two: tile t = (grid, k1, x tile), persistent with the next tile's points
