@@ -38,6 +38,26 @@ struct Plan1D {
     static constexpr int min_radix = sched_min_radix(sc);
 };
 
+// Workgroups of one launch: HIP takes fewer than 2^32 work items in a
+// dimension, and a workgroup has at most 1024.  Grids of more go round a loop
+// in the kernel or take several launches
+// (launch_blocks, launch_tiles).
+constexpr long kMaxBlocks = 1L << 21;
+static_assert(kMaxBlocks * 1024 < (1L << 32), "below HIP's limit");
+
+// Launches `blocks` workgroups that know their place by blockIdx.x alone:
+// f(first, workgroups), more than once only beyond kMaxBlocks.
+template <class F>
+inline hipError_t launch_blocks(long blocks, F&& f)
+{
+    hipError_t e = hipSuccess;
+    for (long first = 0; first < blocks && e == hipSuccess; first += kMaxBlocks) {
+        f(first, (unsigned)(blocks - first < kMaxBlocks ? blocks - first : kMaxBlocks));
+        e = hipGetLastError();
+    }
+    return e;
+}
+
 // ---------------------------------------------------------------- accessors --
 
 // LDS tile: address = line * LS + e * ES (float2 units).

@@ -199,9 +199,11 @@ template <int N, int S>
 static hipError_t launch_axis_row(const float2* in, float2* out, const float2* tw, long rows, hipStream_t st)
 {
     const long blocks = (rows + kRowLines - 1) / kRowLines;
-    hipLaunchKernelGGL((k_axis_row<N, S, kRowLines>), dim3((unsigned)blocks), dim3(RowGeom<N, kRowLines>::T), 0, st,
-                       in, out, tw, rows);
-    return hipGetLastError();
+    return launch_blocks(blocks, [&](long first, unsigned grid) {
+        const long r0 = first * kRowLines;
+        hipLaunchKernelGGL((k_axis_row<N, S, kRowLines>), dim3(grid), dim3(RowGeom<N, kRowLines>::T), 0, st, in + r0 * N,
+                           out + r0 * N, tw, rows - r0);
+    });
 }
 
 #define FFT3D_STR_CASE(n)                                                      \

@@ -39,9 +39,11 @@ static hipError_t launch_row_large(const float2* in, float2* out, const float2* 
 {
     constexpr int L = large_rows<N>();
     const long blocks = (rows + L - 1) / L;
-    hipLaunchKernelGGL((k_axis_row<N, S, L>), dim3((unsigned)blocks), dim3(RowGeom<N, L>::T), 0, st, in, out, tw,
-                       rows);
-    return hipGetLastError();
+    return launch_blocks(blocks, [&](long first, unsigned grid) {
+        const long r0 = first * L;
+        hipLaunchKernelGGL((k_axis_row<N, S, L>), dim3(grid), dim3(RowGeom<N, L>::T), 0, st, in + r0 * N, out + r0 * N,
+                           tw, rows - r0);
+    });
 }
 
 #define FFT3D_STR_LARGE_CASE(n)                                                \

@@ -8,15 +8,19 @@ namespace fft3d {
 template <int N, int S>
 static hipError_t launch_cube(const float2* in, float2* out, const float2* tw, long grids, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_cube<N, S>), dim3((unsigned)grids), dim3(CubeGeom<N>::T), 0, st, in, out, tw);
-    return hipGetLastError();
+    return launch_blocks(grids, [&](long first, unsigned n) {
+        hipLaunchKernelGGL((k_cube<N, S>), dim3(n), dim3(CubeGeom<N>::T), 0, st, in + first * (N * N * N),
+                           out + first * (N * N * N), tw);
+    });
 }
 
 template <int N, int S>
 static hipError_t launch_cube_lines(const float2* in, float2* out, const float2*, long grids, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_cube_lines<N, S>), dim3((unsigned)grids), dim3(CubeLines<N>::T), 0, st, in, out);
-    return hipGetLastError();
+    return launch_blocks(grids, [&](long first, unsigned n) {
+        hipLaunchKernelGGL((k_cube_lines<N, S>), dim3(n), dim3(CubeLines<N>::T), 0, st, in + first * (N * N * N),
+                           out + first * (N * N * N));
+    });
 }
 
 #define FFT3D_CUBE_CASE(n)                                                     \

@@ -7,8 +7,10 @@ namespace fft3d {
 template <int N, int S>
 static hipError_t launch_plane(const float2* in, float2* out, const float2* tw, long planes, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_plane<N, S>), dim3((unsigned)planes), dim3(PlaneGeom<N>::T), 0, st, in, out, tw);
-    return hipGetLastError();
+    return launch_blocks(planes, [&](long first, unsigned n) {
+        hipLaunchKernelGGL((k_plane<N, S>), dim3(n), dim3(PlaneGeom<N>::T), 0, st, in + first * (N * N),
+                           out + first * (N * N), tw);
+    });
 }
 
 template <int N, int S>

@@ -120,40 +120,42 @@ KernelInfo q16_info(int n)
 hipError_t launch_quantize(int fmt, const float2* in, long rows, int C, unsigned* pay, signed char* ex,
                            hipStream_t st)
 {
-    const long blocks = (rows + 3) / 4;
-    if (blocks == 0) return hipSuccess;
-    if (fmt == kFmtF16)
-        hipLaunchKernelGGL(k_q16_quantize<kFmtF16>, dim3((unsigned)blocks), dim3(256), 0, st, in, rows, C, pay, ex);
-    else
-        hipLaunchKernelGGL(k_q16_quantize<kFmtBF16>, dim3((unsigned)blocks), dim3(256), 0, st, in, rows, C, pay, ex);
-    return hipGetLastError();
+    return launch_blocks((rows + 3) / 4, [&](long first, unsigned grid) {   // four rows a workgroup
+        const long r0 = 4 * first;
+        if (fmt == kFmtF16)
+            hipLaunchKernelGGL(k_q16_quantize<kFmtF16>, dim3(grid), dim3(256), 0, st, in + r0 * C, rows - r0, C,
+                               pay + r0 * C, ex + r0);
+        else
+            hipLaunchKernelGGL(k_q16_quantize<kFmtBF16>, dim3(grid), dim3(256), 0, st, in + r0 * C, rows - r0, C,
+                               pay + r0 * C, ex + r0);
+    });
 }
 
 hipError_t launch_dequantize(int fmt, const unsigned* pay, const signed char* ex, long rows, int C, float2* out,
                              hipStream_t st)
 {
-    const long blocks = (rows * C + 255) / 256;
-    if (blocks == 0) return hipSuccess;
     if (C % 2 == 0 && C > 2) {   // every row of payloads starts on 8 bytes, every row of values on 16
         const int Q = C / 2, rpb = Q >= kDequantPairs ? 1 : kDequantPairs / Q;
         const int parts = Q > kDequantPairs ? (Q - 1) / kDequantPairs + 1 : 1;
         const unsigned magic = (unsigned)(((1ull << 32) + Q - 1) / Q);
-        const dim3 grid((unsigned)((rows + rpb - 1) / rpb * parts));
         const uint2* p2 = reinterpret_cast<const uint2*>(pay);
+        return launch_blocks((rows + rpb - 1) / rpb * parts, [&](long first, unsigned grid) {
+            if (fmt == kFmtF16)
+                hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, rpb, parts,
+                                   magic, (unsigned)first, out);
+            else
+                hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, rpb,
+                                   parts, magic, (unsigned)first, out);
+        });
+    }
+    return launch_blocks((rows * C + 255) / 256, [&](long first, unsigned grid) {
         if (fmt == kFmtF16)
-            hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, parts, magic,
+            hipLaunchKernelGGL(k_q16_dequantize<kFmtF16>, dim3(grid), dim3(256), 0, st, pay, ex, rows, C, first * 256,
                                out);
         else
-            hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, grid, dim3(256), 0, st, p2, ex, rows, Q, rpb, parts, magic,
+            hipLaunchKernelGGL(k_q16_dequantize<kFmtBF16>, dim3(grid), dim3(256), 0, st, pay, ex, rows, C, first * 256,
                                out);
-        return hipGetLastError();
-    }
-    if (fmt == kFmtF16)
-        hipLaunchKernelGGL(k_q16_dequantize<kFmtF16>, dim3((unsigned)blocks), dim3(256), 0, st, pay, ex, rows, C, out);
-    else
-        hipLaunchKernelGGL(k_q16_dequantize<kFmtBF16>, dim3((unsigned)blocks), dim3(256), 0, st, pay, ex, rows, C,
-                           out);
-    return hipGetLastError();
+    });
 }
 
 }  // namespace fft3d

@@ -1172,12 +1172,6 @@ inline AxisMap in_runs(AxisMap m, long tiles, int L, bool with_V)
     return m;
 }
 
-// Workgroups of one launch: HIP takes fewer than 2^32 work items in a
-// dimension, and a workgroup has at most 1024.  Grids of more go round a loop
-// in the kernel or take several launches (launch_tiles).
-constexpr long kMaxBlocks = 1L << 21;
-static_assert(kMaxBlocks * 1024 < (1L << 32), "below HIP's limit");
-
 // Launches a strided pass of `tiles` tiles: f(map, workgroups), more than once
 // only for grids beyond kMaxBlocks, the last tiles first as in z_tile.
 template <class F>

@@ -868,12 +868,12 @@ constexpr int kDequantPairs = 2048;
 template <int FMT>
 __global__ void __launch_bounds__(256) k_q16_dequantize2(const uint2* __restrict__ pay, const signed char* __restrict__ ex,
                                                          long rows, int Q, int rpb, int parts, unsigned magic,
-                                                         float2* __restrict__ out)
+                                                         unsigned first, float2* __restrict__ out)
 {
     constexpr int U = 4;
     typedef float f4v __attribute__((ext_vector_type(4)));
-    const unsigned set = blockIdx.x / parts;
-    const int p0 = (int)(blockIdx.x - set * parts) * kDequantPairs;   // first pair in its rows
+    const unsigned block = first + blockIdx.x, set = block / parts;
+    const int p0 = (int)(block - set * parts) * kDequantPairs;   // first pair in its rows
     const long r0 = (long)set * rpb;
     const int nr = (int)(rows - r0 < rpb ? rows - r0 : rpb), left = nr * Q - p0;
     const int n = left < kDequantPairs ? left : kDequantPairs;
@@ -902,12 +902,12 @@ __global__ void __launch_bounds__(256) k_q16_dequantize2(const uint2* __restrict
     }
 }
 
-// Any row length: one point a thread.
+// Any row length: one point a thread, from point i0 on.
 template <int FMT>
 __global__ void __launch_bounds__(256) k_q16_dequantize(const unsigned* pay, const signed char* ex, long rows, int C,
-                                                        float2* out)
+                                                        long i0, float2* out)
 {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    const long i = i0 + (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= rows * C) return;
     const int e = ex[i / C];
     const unsigned u = pay[i];

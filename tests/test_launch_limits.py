@@ -82,3 +82,42 @@ def test_strided_tiles(F, n, b):
         del y
     assert E.item() == pytest.approx(E_few.item(), rel=1e-12)
     assert F.energy(x, V).item() == pytest.approx(E_few.item(), rel=1e-12)
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_whole_grids(F, n):
+    """2^26 grids and a few of one workgroup each."""
+    b = (1 << 26) + 5
+    x, at = grids((b, n, n, n), 5)
+    few = torch.stack([x[k] for k in at])
+    F.Plan(n, n, n, b, "fp32", -1).exec(x, x)
+    want = F.Plan(n, n, n, len(at), "fp32", -1).exec(few)
+    for j, k in enumerate(at):
+        assert torch.equal(x[k], want[j]), k
+
+
+def test_rows(F):
+    """2^26 tiles of 16 short rows and a few."""
+    b = 360000000
+    x, at = grids((b, 1, 3, 2), 17)
+    few = torch.stack([x[k] for k in at])
+    plan = F.Plan(2, 3, 1, b, "fp32", -1)
+    assert "k_axis_row" in plan.describe()
+    plan.exec(x, x)
+    want = F.Plan(2, 3, 1, len(at), "fp32", -1).exec(few)
+    for j, k in enumerate(at):
+        assert torch.equal(x[k], want[j]), k
+
+
+@pytest.mark.parametrize("rows,C", [((1 << 32) + 777, 1), ((1 << 26) + 9, 4)])
+@pytest.mark.parametrize("precision", ["fp16", "bf16"])
+def test_scaled_rows(F, rows, C, precision):
+    """Conversion to 16 bits and back of more rows than a launch has waves."""
+    x, at = grids((rows, C), 100 if C == 1 else 8)
+    few = torch.stack([x[k] for k in at])
+    buf = F.quantize(x, precision)
+    del x
+    back = F.dequantize(buf, (rows, C), precision)
+    want = F.dequantize(F.quantize(few, precision), few.shape, precision)
+    for j, k in enumerate(at):
+        assert torch.equal(back[k], want[j]), k
