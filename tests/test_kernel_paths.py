@@ -409,3 +409,106 @@ def test_in_place_above_128(F, n, b, sign):
     y = plan.exec(x)
     plan.exec(x, x)
     assert torch.equal(x, y)
+
+
+def run_of(lines, es, tiles, with_V):
+    """Tiles of an XCD's run by the rule of the strided passes of 64 lines; 0: launch order."""
+    gains = es % 16 != 0 or (with_V and lines % 512 != 0)
+    return (lines + 256) // 512 if gains and tiles >= 512 and lines >= 256 else 0
+
+
+# whole groups of eight runs and a rest, rests of a few tiles and of most of a group
+RUNS = [(30, 3, 40), (50, 2, 14), (90, 2, 5), (90, 3, 13)]
+
+
+def run_case(n, nz, b, cut, with_V):
+    tiles = (n * n * b + 63) // 64
+    run = run_of(n * n, n * n, tiles, with_V)
+    assert run >= 2 and tiles > 8 * run and tiles % (8 * run)     # permuted, and a part that is not
+    r2 = (0.3 * n) ** 2
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + workloads.signed_freq(nz)[:, None, None] ** 2) < r2
+    c = workloads.uniform_grid((n, n, nz), 1500 + n, batch=b)
+    V = (workloads.uniform_grid((n, n, nz), 1600 + n).real + 1.5).astype(np.float32)
+    return r2, inside, (c * inside).astype(np.complex64) if cut else c, V
+
+
+@pytest.mark.parametrize("n,nz,b,cut", [c + (cut,) for c in RUNS for cut in (False, True)] + [(72, 2, 7, False)])
+def test_operator_in_runs_of_tiles(F, n, nz, b, cut):
+    """The operator's z pass and the energies with tiles dealt in runs of two
+    or more (72 points: rows of whole cache lines, only V gains by it)."""
+    r2, inside, c, V = run_case(n, nz, b, cut, not cut)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    if cut:
+        plan.set_cutoff(r2)
+    x, v = torch.from_numpy(c).cuda(), torch.from_numpy(V).cuda()
+    E = torch.zeros((), dtype=torch.float64, device="cuda")
+    out = plan.apply_potential(x, v, E=E).cpu().numpy()
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    want = np.fft.fftn(V.astype(np.float64) * psi, axes=(1, 2, 3))
+    if cut:
+        out, want = out[:, inside], want[:, inside]
+    for k in range(b):
+        assert rel(out[k], want[k]) <= TOL, k
+    E_ref = float((V.astype(np.float64) * np.abs(psi) ** 2).sum())
+    assert abs(E.item() - E_ref) <= 1e-6 * E_ref
+    if not cut:
+        E2, psi2 = F.energy_and_psi(x, v)
+        assert abs(E2.item() - E_ref) <= 1e-6 * E_ref and abs(F.energy(x, v).item() - E_ref) <= 1e-6 * E_ref
+        for k in range(b):
+            assert rel(psi2[k].cpu().numpy(), psi[k]) <= TOL, k
+
+
+@pytest.mark.parametrize("n,nz,b", RUNS)
+def test_transforms_in_runs_of_tiles(F, n, nz, b):
+    """The dense, pruned and packed z passes, both signs, likewise."""
+    r2, inside, c, _ = run_case(n, nz, b, True, False)
+    full = workloads.uniform_grid((n, n, nz), 1700 + n, batch=b)
+    psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
+    spec = np.fft.fftn(full.astype(np.complex128), axes=(1, 2, 3))
+    inv, fwd = F.Plan(n, n, nz, b, "fp32", INVERSE), F.Plan(n, n, nz, b, "fp32", FORWARD)
+    x, f = torch.from_numpy(c).cuda(), torch.from_numpy(full).cuda()
+    dense = [(inv.exec(x), psi), (fwd.exec(f), spec)]
+    inv.set_cutoff(r2)
+    fwd.set_cutoff(r2)
+    dense.append((inv.exec(x), psi))
+    packed = torch.from_numpy(np.ascontiguousarray(c[:, inside])).cuda()
+    dense.append((inv.exec_packed(torch.full_like(x, complex("nan")), packed), psi))
+    pruned = fwd.exec(f).cpu().numpy()[:, inside]
+    got = torch.full((b, fwd.sphere_points), complex("nan"), dtype=torch.complex64, device="cuda")
+    fwd.exec_packed(f.clone(), got)
+    for y, want in dense + [(torch.from_numpy(pruned), spec[:, inside]), (got, spec[:, inside])]:
+        y = y.cpu().numpy()
+        for k in range(b):
+            assert rel(y[k], want[k]) <= TOL, k
+
+
+@pytest.mark.parametrize("n,nz,b", [(90, 3, 9), (50, 2, 27)])
+def test_real_grids_in_runs_of_tiles(F, n, nz, b):
+    """The z pass over half spectra, rows of n / 2 + 1 points."""
+    half = n // 2 + 1
+    assert run_of(half * n, half * n, (half * n * b + 63) // 64, False) >= 2
+    rho = workloads.uniform_grid((n, n, nz), 1800 + n, batch=b).real.astype(np.float32)
+    want = np.fft.rfftn(rho.astype(np.float64), axes=(1, 2, 3))
+    h = F.rfftn(torch.from_numpy(rho).cuda())
+    back = F.irfftn(h, n).cpu().numpy() / (n * n * nz)
+    for k in range(b):
+        assert rel(h[k].cpu().numpy(), want[k]) <= TOL, k
+        assert rel(back[k], rho[k]) <= TOL, k
+
+
+@pytest.mark.parametrize("n,b", [(10, 512), (10, 515), (12, 513), (12, 600)])
+@pytest.mark.parametrize("sign", [INVERSE, FORWARD])
+def test_whole_grid_lines_of_10_and_12(F, n, b, sign):
+    """The two lengths of the whole-grid kernel whose last wave has idle lanes
+    and whose exchanges move whole points; in place too."""
+    x = workloads.uniform_grid(n, 1900 + n, batch=b)
+    plan = F.Plan(n, n, n, b, "fp32", sign)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert plan.describe().startswith("cube lines") == (b >= 2 * cus)
+    xt = torch.from_numpy(x).cuda()
+    y = plan.exec(xt)
+    plan.exec(xt, xt)
+    assert torch.equal(y, xt)
+    for j in {0, b // 2, b - 1}:
+        assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
