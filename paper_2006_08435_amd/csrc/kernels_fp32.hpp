@@ -1628,6 +1628,7 @@ k_axis_density(float2* buf, const float2* __restrict__ tw, AxisMap m, long vol,
     // stage 0 (radix R0, no twiddles) is split into its loads, issued one
     // orbital ahead into registers, and its butterflies
     constexpr int R0 = P::radix(0), M0 = N / R0, NB0 = L * M0, IT0 = (NB0 + T - 1) / T;
+    static_assert(P::stages > 1 || NB0 <= 64, "a single stage has no barrier: one wave loads before it stores its sums");
     __shared__ float2 lds[G::WORDS];
     const int tid = threadIdx.x;
     // tiles of fewer than 64 lines read their twiddles per lane: from an LDS
