@@ -35,6 +35,27 @@ namespace fft3d {
     X(135) X(144) X(150) X(160) X(162) X(180) X(192) X(200) X(216) X(240)      \
     X(256)
 
+// The list holds exactly the lengths that the rule accepts.
+constexpr bool split_listed(int n)
+{
+#define FFT3D_SPLIT_LISTED(m) if (n == m) return true;
+    FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_LISTED)
+#undef FFT3D_SPLIT_LISTED
+    return false;
+}
+constexpr bool split_list_is_rule()
+{
+    for (int n = 129; n <= 256; ++n) {
+        int m = n;
+        while (m % 2 == 0) m /= 2;
+        while (m % 3 == 0) m /= 3;
+        while (m % 5 == 0) m /= 5;
+        if (m == 1 && split_ok(n) != split_listed(n)) return false;
+    }
+    return true;
+}
+static_assert(split_list_is_rule(), "FFT3D_FOR_EACH_SPLIT_SIZE and split_ok");
+
 template <int N>
 struct SplitGeom {
     static_assert(split_ok(N), "a length of the two-pass form");

@@ -167,9 +167,11 @@ __host__ __device__ constexpr Sched make_sched_rev(int n)
 
 // Two-pass form of cubic grids above 128 points a side (kernels_split.hpp).
 // Points of x a z tile for R parts: 32 (256 bytes a run) where that tile then
-// has at most 13000 points, else 16.
+// has at most 13000 points, else 16.  A tile has at most 16384 points (131 KB
+// of LDS beside the table); a larger one, as the 18000 points that 225 would
+// need, was never built or measured.
 __host__ __device__ constexpr int split_lines(int n, int r) { return 32 * r * n <= 13000 ? 32 : 16; }
-__host__ __device__ constexpr bool split_z_fits(int n, int r) { return split_lines(n, r) * r * n <= 18432; }
+__host__ __device__ constexpr bool split_z_fits(int n, int r) { return split_lines(n, r) * r * n <= 16384; }
 
 // The parts R of a plane: the fewest whose tile has at most 12300 points, so
 // that its next rows (12 points a thread) stay in registers beside two turns
