@@ -93,10 +93,13 @@ enum fft3d_status {
  * radix schedule, generates the twiddle factors in double precision (rounded
  * once to the working precision) and uploads them to the current device.
  * Grids with a dimension above 128 (the larger sizes the paper names as
- * future work, Section III) use the three-pass form: one 1D pass per axis
- * (x rows, then strided y and z lines), FP32 only (FFT3D_E_UNSUPPORTED for
- * the scaled 16-bit precisions); every other entry point that takes a plan
- * (energy, cutoff, real grids, heterogeneous batches) is limited to 128.
+ * future work, Section III) are FP32 only (FFT3D_E_UNSUPPORTED for the scaled
+ * 16-bit precisions); every other entry point that takes a plan (energy,
+ * cutoff, real grids, heterogeneous batches) is limited to 128.  Their passes:
+ * most cubes of 135 to 256 points a side take two, an xy-plane pass in parts
+ * and a z pass (in place three: x rows, y and z lines, the same result); planes
+ * of at most 128 x 128 under a longer z take the plane pass and the z pass; the
+ * others one 1D pass per axis.  fft3d_plan_describe names the kernels.
  * Returns NULL on error (see fft3d_last_error).
  */
 fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int direction);

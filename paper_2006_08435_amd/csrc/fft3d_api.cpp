@@ -22,7 +22,7 @@ thread_local int g_last_error = FFT3D_OK;
 enum Scheme {
     kCube = 0,    // whole grid per workgroup, radix stages in LDS (cubic, up to 16)
     kPlaneZ = 1,  // xy-plane pass + strided z pass (Nx == Ny)
-    kAxes = 2,    // x rows, strided y, strided z
+    kAxes = 2,    // lengths apart: planes of unequal sides or the split form, then z; else x rows, y, z
     kFused = 3,   // persistent plane + z-slab kernel (cubic)
     kCubeLines = 5, // whole grid per workgroup, a line a thread (cubic, 8 to 32)
     kQ16 = 4,     // scaled 16-bit storage, radix-16 on the matrix cores (cubic, 16 | N)
@@ -129,7 +129,7 @@ fft3d_plan_t fft3d_plan(int nx, int ny, int nz, int batch, int precision, int di
         set_error(FFT3D_E_UNSUPPORTED_SIZE);
         return nullptr;
     }
-    // lengths above 128: FP32, three-pass form only
+    // lengths above 128: FP32, the forms of kAxes only
     const bool large = nx > 128 || ny > 128 || nz > 128;
     if (large && precision != FFT3D_FP32) { set_error(FFT3D_E_UNSUPPORTED); return nullptr; }
     const long vol = (long)nx * ny * nz;
@@ -1053,6 +1053,26 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
                  p->nx, radices(p->nx).c_str(), a.threads, a.lds_bytes, (long)p->batch * p->nz, p->nz,
                  radices(p->nz).c_str(), b.threads, b.lds_bytes);
         d = tmp;
+    } else if (p->passes.size() && p->passes[0].kind == Pass::kSplitPlaneK) {
+        const KernelInfo a = split_plane_info(p->nx), b = split_z_info(p->nx), c = split_cols_info(p->ny);
+        const int parts = split_parts_of(p->nx);
+        snprintf(tmp, sizeof tmp,
+                 "axes split n=%d parts=%d plane(x %s, y %s, t%d, lds %d) z(y %d, z %s, t%d, lds %d) in place: "
+                 "x(%s,t%d) y(%sx%d,t%d) z(%s,t%d)",
+                 p->nx, parts, radices(p->nx).c_str(), radices(p->ny / parts).c_str(), a.threads, a.lds_bytes, parts,
+                 radices(p->nz).c_str(), b.threads, b.lds_bytes, radices(p->nx).c_str(), axis_row_info(p->nx).threads,
+                 radices(p->ny / parts).c_str(), parts, c.threads, radices(p->nz).c_str(),
+                 axis_str_info(p->nz).threads);
+        d = tmp;
+    } else if (p->passes.size() && p->passes[0].kind == Pass::kRectK) {
+        const KernelInfo a = rect_info(p->nx, p->ny), b = axis_str_info(p->nz);
+        snprintf(tmp, sizeof tmp, "axes plane x=%d(%s) y=%d(%s) threads=%d lds=%d planes=%ld", p->nx,
+                 radices(p->nx).c_str(), p->ny, radices(p->ny).c_str(), a.threads, a.lds_bytes, p->passes[0].count);
+        d = tmp;
+        if (p->nz > 1) {
+            snprintf(tmp, sizeof tmp, "; z=%d(%s,t%d)", p->nz, radices(p->nz).c_str(), b.threads);
+            d += tmp;
+        }
     } else {
         const KernelInfo a = axis_row_info(p->nx), b = axis_str_info(p->ny), c = axis_str_info(p->nz);
         snprintf(tmp, sizeof tmp, "axes x=%d(%s,t%d) y=%d(%s,t%d) z=%d(%s,t%d)", p->nx, radices(p->nx).c_str(),

@@ -50,6 +50,11 @@ bool rect_init(int nx, int ny, long planes, int sign)
     return true;
 }
 
+KernelInfo rect_info(int nx, int ny)
+{
+    return {kRectClasses[rect_class(nx, ny)].threads, rect_lds_bytes(nx, ny)};   // of a plane that rect_init took
+}
+
 hipError_t launch_plane_rect(const float2* in, float2* out, const float2* tw_x, const float2* tw_y, int nx, int ny,
                              long planes, int sign, hipStream_t st)
 {

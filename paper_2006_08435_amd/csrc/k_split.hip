@@ -87,6 +87,40 @@ AxisVarFn split_cols_fn(int n, int sign)
     }
 }
 
+#define FFT3D_SPLIT_INFO_PLANE(n)                                              \
+    case n:                                                                    \
+        return {SplitGeom<n>::T, (int)sizeof(float2) * SplitGeom<n>::PLANE_WORDS};
+#define FFT3D_SPLIT_INFO_Z(n)                                                  \
+    case n:                                                                    \
+        return {SplitGeom<n>::T, (int)sizeof(float2) * SplitGeom<n>::Z_WORDS};
+#define FFT3D_SPLIT_INFO_COLS(n)                                               \
+    case n:                                                                    \
+        return {AxisGeom<n, 32, 4>::T, (int)sizeof(float2) * AxisGeom<n, 32, 4>::WORDS};
+
+KernelInfo split_plane_info(int n)
+{
+    switch (n) {
+        FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_INFO_PLANE)
+    default: return {0, 0};
+    }
+}
+
+KernelInfo split_z_info(int n)
+{
+    switch (n) {
+        FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_INFO_Z)
+    default: return {0, 0};
+    }
+}
+
+KernelInfo split_cols_info(int n)
+{
+    switch (n) {
+        FFT3D_FOR_EACH_SPLIT_SIZE(FFT3D_SPLIT_INFO_COLS)
+    default: return {0, 0};
+    }
+}
+
 // A tile above 12300 points that is not whole turns (240) spills registers in
 // the plane pass: it pays only where input and output are twice the 256 MB Infinity
 // Cache and the third pass costs HBM traffic (240^3, inverse + forward: one

@@ -62,9 +62,9 @@ struct SplitGeom {
     static constexpr int R = split_parts(N), N1 = N / R, L = split_lines(N, R);
     static constexpr int T = 1024;
     // plane tile: N1 rows of N points
-    static constexpr int RS = odd_stride(N);
+    static constexpr int RS = odd_stride(N), PLANE_WORDS = N1 * RS;
     // z tile: N rows of R * L lines (the x points of k2 = 0, of k2 = 1, ...)
-    static constexpr int LINES = R * L, LP = odd_stride(LINES);
+    static constexpr int LINES = R * L, LP = odd_stride(LINES), Z_WORDS = N * LP;
     static constexpr int XT = (N + L - 1) / L;   // tiles along x, the last one ragged
     static constexpr int VEC = N % 2 == 0 ? 2 : 1;
 };
@@ -120,7 +120,7 @@ k_split_plane(const float2* in, float2* out, const float2* __restrict__ tw_x, co
 {
     using G = SplitGeom<N>;
     constexpr int R = G::R, N1 = G::N1, T = G::T, RS = G::RS;
-    __shared__ float2 lds[N1 * RS];
+    __shared__ float2 lds[G::PLANE_WORDS];
     // lines not a multiple of 64: a wave's butterflies span two twiddle groups
     // and read them per lane, from an LDS copy
     constexpr bool TWX = N1 % 64 != 0, TWY = N % 64 != 0;
@@ -210,7 +210,7 @@ k_split_z(const float2* in, float2* out, const float2* __restrict__ tw_z, const 
 {
     using G = SplitGeom<N>;
     constexpr int R = G::R, N1 = G::N1, T = G::T, L = G::L, LINES = G::LINES, LP = G::LP, XT = G::XT, VEC = G::VEC;
-    __shared__ float2 lds[N * LP];
+    __shared__ float2 lds[G::Z_WORDS];
     constexpr bool TWZ = LINES % 64 != 0;
     constexpr int NZ = Plan1D<N>::tw_len;
     __shared__ float2 tw_lds[TWZ && NZ > 0 ? NZ : 1];

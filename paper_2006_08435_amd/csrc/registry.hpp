@@ -180,12 +180,16 @@ struct KernelInfo {
 };
 KernelInfo cube_info(int n);
 KernelInfo cube_lines_info(int n);
+KernelInfo rect_info(int nx, int ny);
+KernelInfo split_plane_info(int n);
+KernelInfo split_z_info(int n);
+KernelInfo split_cols_info(int n);
 KernelInfo plane_info(int n);
 KernelInfo axis_str_info(int n);
 KernelInfo axis_row_info(int n);
 KernelInfo fused_info(int n);
 KernelInfo q16_info(int n);
-// Lengths above 128 (three-pass form only); axis_str_fn / axis_row_fn and
+// Lengths above 128 (1D passes); axis_str_fn / axis_row_fn and
 // their _info functions forward to these for n > 128.
 AxisStrFn axis_str_large_fn(int n, int sign);
 AxisRowFn axis_row_large_fn(int n, int sign);

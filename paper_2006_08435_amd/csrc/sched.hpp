@@ -253,7 +253,7 @@ __host__ __device__ constexpr bool smooth235(int n)
 // Lengths of every form: 2*3*5-smooth, 1..128.
 __host__ __device__ constexpr bool size_supported(int n) { return n <= 128 && smooth235(n); }
 
-// Lengths of the three-pass form only (one line of up to 512 points per
+// Lengths of the 1D passes and the split form only (one line of up to 512 points per
 // transform, lines of 16..32 per workgroup): 2*3*5-smooth, 129..512.
 __host__ __device__ constexpr bool size_supported_large(int n) { return n > 128 && n <= 512 && smooth235(n); }
 
@@ -273,7 +273,7 @@ __host__ __device__ constexpr bool size_supported_large(int n) { return n > 128 
     X(60) X(64) X(72) X(75) X(80) X(81) X(90) X(96) X(100) X(108) X(120)       \
     X(125) X(128)
 
-// X-macro over the lengths of the three-pass form above 128.
+// X-macro over the lengths above 128.
 #define FFT3D_FOR_EACH_LARGE_SIZE(X)                                           \
     X(135) X(144) X(150) X(160) X(162) X(180) X(192) X(200) X(216) X(225)      \
     X(240) X(243) X(250) X(256) X(270) X(288) X(300) X(320) X(324) X(360)      \

@@ -512,3 +512,21 @@ def test_whole_grid_lines_of_10_and_12(F, n, b, sign):
     assert torch.equal(y, xt)
     for j in {0, b // 2, b - 1}:
         assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), sign)) <= TOL
+
+
+@pytest.mark.parametrize("shape,text", [
+    ((100, 72, 90), "axes plane x=100(10x10) y=72(12x6) threads=512 lds="),
+    ((128, 125, 1), "axes plane x=128(8x16) y=125(5x5x5) threads=1024 lds="),
+    ((10, 4, 160), "axes plane x=10(10) y=4(4) threads=128 lds="),
+    ((256, 256, 256), "axes split n=256 parts=4 plane(x 16x16, y 8x8, t1024, lds 131584) z(y 4, z 16x16, t1024, lds 133120)"),
+    ((135, 135, 135), "axes split n=135 parts=3 plane(x "),
+    ((250, 250, 250), "axes x=250("),
+])
+def test_describe_names_the_kernels_that_run(F, shape, text):
+    """Threads, radices and LDS of the plane kernels, not of the 1D passes."""
+    d = F.Plan(*shape, 1, "fp32", INVERSE).describe()
+    assert d.startswith(text), d
+    kernels = d.split("kernels=")[1].split(",")
+    assert kernels[0] == ("k_plane_rect" if "plane x=" in d else "k_split_plane" if "split" in d else "k_axis_row")
+    if "plane x=" in d:
+        assert ("; z=%d(" % shape[2] in d) == (shape[2] > 1) and ("k_axis_str" in kernels) == (shape[2] > 1)
