@@ -834,8 +834,8 @@ k_sphere_pack(const float2* __restrict__ src, float2* __restrict__ dst, const Sp
     }
 }
 
-// Packed spheres -> dense grids, zeros outside: a workgroup writes one
-// xy-plane, VEC = 2 (nx even) 16 bytes a lane.  Bound by those writes:
+// Packed spheres -> dense grids, zeros outside: the workgroups of blockIdx.x
+// write one xy-plane, VEC = 2 (nx even) 16 bytes a lane.  Bound by those writes:
 // planes outside the sphere read nothing, the others their row table.
 // 64 x 90^3 (373 MB written): 133 us with 8 bytes a lane and a 64-bit
 // division a point -> 85 us.  (Streaming stores: 88 us, and the pass that
@@ -852,7 +852,7 @@ k_sphere_unpack(const float2* __restrict__ src, float2* __restrict__ dst, const 
         float2* plane = dst + p * ((long)ny * nx);
         const float2* sphere = src + b * npts;
         const bool hit = (double)(gz * gz) < R2;   // uniform
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < n; i += gridDim.y * blockDim.x) {
             float2 v[VEC];
 #pragma unroll
             for (int k = 0; k < VEC; ++k) v[k] = make_float2(0.f, 0.f);

@@ -530,3 +530,50 @@ def test_describe_names_the_kernels_that_run(F, shape, text):
     assert kernels[0] == ("k_plane_rect" if "plane x=" in d else "k_split_plane" if "split" in d else "k_axis_row")
     if "plane x=" in d:
         assert ("; z=%d(" % shape[2] in d) == (shape[2] > 1) and ("k_axis_str" in kernels) == (shape[2] > 1)
+
+
+@pytest.mark.parametrize("n,nz,b,r2", [(24, 2, 1, 36.0), (32, 1, 1, 1e9), (125, 3, 1, 900.0), (128, 8, 2, 900.0),
+                                       (16, 3, 683, 16.0), (30, 5, 409, 30.0), (30, 5, 410, 30.0)])
+def test_unpack_planes_shared_by_workgroups(F, n, nz, b, r2):
+    """Few planes (many workgroups each, the last ones with fewer units) to
+    more than 2048 (one each): bit for bit."""
+    gz = workloads.signed_freq(nz)[:, None, None]
+    g = workloads.signed_freq(n)
+    inside = (g[None, None, :] ** 2 + g[None, :, None] ** 2 + gz ** 2) < r2
+    x = workloads.uniform_grid((n, n, nz), 2200 + n, batch=b)
+    plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
+    plan.set_cutoff(r2)
+    dense = torch.full((b, nz, n, n), complex("nan"), dtype=torch.complex64, device="cuda")
+    got = plan.unpack(torch.from_numpy(np.ascontiguousarray(x[:, inside])).cuda(), dense).cpu().numpy()
+    assert np.array_equal(got.view(np.uint64), np.where(inside[None], x, np.complex64(0)).view(np.uint64))
+
+
+def best_replay(call, calls=10):
+    """Milliseconds of `calls` calls, the best of several replays of a graph."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            call()
+    times = []
+    for _ in range(6):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        graph.replay()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(end))
+    return min(times)
+
+
+def test_unpack_time_of_few_grids(F):
+    """One grid of 125^3 in a fifth of the time of sixteen at most (a workgroup
+    a plane takes a third of it)."""
+    def best(b):
+        plan = F.Plan(125, 125, 125, b, "fp32", INVERSE)
+        plan.set_cutoff((125 / 4) ** 2)
+        dense = torch.zeros(plan.shape, dtype=torch.complex64, device="cuda")
+        packed = plan.pack(dense)
+        return best_replay(lambda: plan.unpack(packed, dense))
+    assert 5 * best(1) < best(16)
