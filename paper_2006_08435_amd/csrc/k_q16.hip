@@ -135,16 +135,15 @@ hipError_t launch_dequantize(int fmt, const unsigned* pay, const signed char* ex
                              hipStream_t st)
 {
     if (C % 2 == 0 && C > 2) {   // every row of payloads starts on 8 bytes, every row of values on 16
-        const int Q = C / 2, rpb = Q >= kDequantPairs ? 1 : kDequantPairs / Q;
-        const int parts = Q > kDequantPairs ? (Q - 1) / kDequantPairs + 1 : 1;
+        const int Q = C / 2, per = dequant_pairs(rows * Q), rpb = Q >= per ? 1 : per / Q, parts = (Q - 1) / per + 1;
         const unsigned magic = (unsigned)(((1ull << 32) + Q - 1) / Q);
         const uint2* p2 = reinterpret_cast<const uint2*>(pay);
         return launch_blocks((rows + rpb - 1) / rpb * parts, [&](long first, unsigned grid) {
             if (fmt == kFmtF16)
-                hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, rpb, parts,
-                                   magic, (unsigned)first, out);
+                hipLaunchKernelGGL(k_q16_dequantize2<kFmtF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, per, rpb,
+                                   parts, magic, (unsigned)first, out);
             else
-                hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, rpb,
+                hipLaunchKernelGGL(k_q16_dequantize2<kFmtBF16>, dim3(grid), dim3(256), 0, st, p2, ex, rows, Q, per, rpb,
                                    parts, magic, (unsigned)first, out);
         });
     }

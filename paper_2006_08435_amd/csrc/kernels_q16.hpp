@@ -855,7 +855,7 @@ __global__ void __launch_bounds__(256) k_q16_quantize(const float2* in, long row
 
 // Rows of an even number of points: a lane converts pairs, one 8-byte load and
 // one 16-byte store each, four pairs in flight.  A workgroup takes `rpb` whole
-// rows (Q = C / 2 pairs each, rpb * Q <= kDequantPairs), so a pair's row is a
+// rows (Q = C / 2 pairs each, rpb * Q <= per), so a pair's row is a
 // 32-bit quotient: magic = ceil(2^32 / Q) is exact for the pairs of a
 // workgroup.  A row of more pairs is shared by `parts` workgroups (rpb = 1)
 // with one exponent each, so that a few long rows fill the device too (one
@@ -864,19 +864,30 @@ __global__ void __launch_bounds__(256) k_q16_quantize(const float2* in, long row
 // with one point and a 64-bit division a thread, 159 with four points a lane
 // (its two stores each cover half of every cache line), 116 so.
 constexpr int kDequantPairs = 2048;
+// Pairs of a workgroup (`per`): two turns of four a thread, or fewer where that
+// would leave less than 256 workgroups, one a compute unit.  Two turns follow
+// each other, so 256 x 16, 2304 x 48 and 9216 x 48 points took 2.5, 2.7 and
+// 3.1 us with 2048 pairs each, so 2.3, 2.3 and 2.8 (one point a thread: 2.3, 2.3,
+// 2.7); 16384 x 64, the least for 2048 pairs, 3.9, with 256 pairs 4.1.
+constexpr int dequant_pairs(long pairs)
+{
+    int per = kDequantPairs;
+    while (per > 256 && pairs < 256L * per) per /= 2;
+    return per;
+}
 
 template <int FMT>
 __global__ void __launch_bounds__(256) k_q16_dequantize2(const uint2* __restrict__ pay, const signed char* __restrict__ ex,
-                                                         long rows, int Q, int rpb, int parts, unsigned magic,
+                                                         long rows, int Q, int per, int rpb, int parts, unsigned magic,
                                                          unsigned first, float2* __restrict__ out)
 {
     constexpr int U = 4;
     typedef float f4v __attribute__((ext_vector_type(4)));
     const unsigned block = first + blockIdx.x, set = block / parts;
-    const int p0 = (int)(block - set * parts) * kDequantPairs;   // first pair in its rows
+    const int p0 = (int)(block - set * parts) * per;   // first pair in its rows
     const long r0 = (long)set * rpb;
     const int nr = (int)(rows - r0 < rpb ? rows - r0 : rpb), left = nr * Q - p0;
-    const int n = left < kDequantPairs ? left : kDequantPairs;
+    const int n = left < per ? left : per;
     const uint2* src = pay + r0 * Q + p0;
     f4v* dst = reinterpret_cast<f4v*>(out) + r0 * Q + p0;
     for (int i0 = threadIdx.x; i0 < n; i0 += U * 256) {

@@ -362,11 +362,11 @@ def test_captured_and_replayed(F, form):
         assert torch.equal(got, want[k]), k
 
 
-@pytest.mark.parametrize("rows,C", [(1, 4096), (2, 4098), (3, 8192), (2, 8194), (1, 1 << 20)])
+@pytest.mark.parametrize("rows,C", [(1, 4096), (2, 4098), (3, 8192), (2, 8194), (600, 500), (700, 770), (1, 400002), (1, 1 << 20)])
 @pytest.mark.parametrize("precision", ["fp16", "bf16"])
 def test_dequantize_long_rows(F, rows, C, precision):
-    """Rows of one workgroup's pairs, a pair more, two workgroups' and a pair
-    more: payload * 2^exponent, bit for bit."""
+    """Whole and part workgroups of 256, 512, 1024 and 2048 pairs, rows shorter and
+    longer than those: payload * 2^exponent, bit for bit."""
     rng = np.random.default_rng(1400 + rows + C)
     x = workloads.uniform_grid((C, rows, 1), 1400 + rows)[0] * np.exp2(rng.integers(-40, 40, (rows, 1)))
     buf = F.quantize(torch.from_numpy(x.astype(np.complex64)).cuda(), precision)
