@@ -139,14 +139,15 @@ int apply_schedule(fft3d_plan_s* p, int threads, int chunk, const bool* plain = 
 // about kPlainUs each while it is small and the time of its bytes beyond; the
 // persistent launch costs kManyUs, and each of its groups the time of its
 // bytes.  The cheapest of three splits is taken: every group plain, the groups
-// that gain by it in one persistent launch, every group there.  Measured (us;
-// persistent launch of everything / plain launches / this rule):
-//   64^3 x 256 + 48 + 72 + 96 + 100 + 120        420 / 399 / 385 (the five single grids together;
-//                                                421 / 432 / 417 on buffers new to the caches)
-//   100 x 5 + 128 + 72 + 80 x 11 + 96 x 3 + 120 x 5   240 / 187 / plain
-//   36 x 240 + 50 x 145 + 100 x 7              353 / 207 / plain
-//   24 x 25 + 50                                28 /  19 / plain
-//   60 + 40 x 3 + 24 x 5 + 128 x 2 + 90 + 36 x 10      59 /  74 / everything
+// that gain by it in one persistent launch, every group there.  Measured (us, on
+// buffers that change from call to call; persistent launch of everything / plain
+// launches / this rule):
+//   64^3 x 256 + 48 + 72 + 96 + 100 + 120        421 / 432 / 417 (the five single grids together;
+//                                                420 / 399 / 385 on the same buffers again and again)
+//   100 x 5 + 128 + 72 + 80 x 11 + 96 x 3 + 120 x 5   240 / 195 / plain
+//   36 x 240 + 50 x 145 + 100 x 7              355 / 208 / plain
+//   24 x 25 + 50                                27 /  17 / plain
+//   60 + 40 x 3 + 24 x 5 + 128 x 2 + 90 + 36 x 10      62 /  73 / everything
 constexpr double kPlainUs = 6.3, kManyUs = 33.0;
 constexpr double kPlainBytesPerUs = 6.0e6, kManyBytesPerUs = 5.5e6;
 

@@ -353,9 +353,9 @@ k_cube(const float2* in, float2* out, const float2* __restrict__ tw)
 // (real, then imaginary), so that a grid of up to 32^3 (256 KB) passes
 // through 4 bytes a point of LDS.  One read and one write of the grid, where
 // the plane and z passes make two of each.  Measured against those, inverse +
-// forward in us: 1024 x 20^3 89 -> 44, 400 x 27^3 103 -> 49, 400 x 30^3 133 ->
-// 85, 4096 x 32^3 1658 -> 877 (644 at the copy rate); up to 16 points against
-// k_cube: 1024 x 16^3 26.4 -> 22.6.  At 30
+// forward in us, on buffers that change from call to call: 1024 x 20^3 89 -> 55,
+// 400 x 27^3 103 -> 59, 400 x 30^3 133 -> 97, 4096 x 32^3 1617 -> 879 (644 at the
+// copy rate); up to 16 points against k_cube: 1024 x 16^3 28.1 -> 26.5.  At 30
 // and 32 points one workgroup fills a compute unit, and a batch of two turns of
 // the device pays for its ragged last turn.
 template <int N>
@@ -1152,6 +1152,10 @@ struct AxisMap {
     unsigned first = 0;   // first tile of this launch (launch_tiles)
 };
 
+// XCDs of an MI355X in its default partition, dealt workgroups in turn.  On
+// another partition only the order of the tiles is not the best.
+constexpr int kXcds = 8;
+
 // The map of a strided pass of `tiles` tiles of L lines with its order of
 // tiles.  Where rows are not whole cache lines (with_V: or an XCD would meet
 // another part of V in every grid, as 8 L does not divide a grid's lines), the
@@ -1167,8 +1171,8 @@ struct AxisMap {
 inline AxisMap in_runs(AxisMap m, long tiles, int L, bool with_V)
 {
     const long lines = (long)m.nx * m.odiv;   // of a grid
-    const bool gains = m.es % 16 != 0 || (with_V && lines % (8 * L) != 0);
-    m.run = gains && tiles >= 512 && lines >= 4 * L ? (int)((lines + 4 * L) / (8 * L)) : 0;
+    const bool gains = m.es % 16 != 0 || (with_V && lines % (kXcds * L) != 0);
+    m.run = gains && tiles >= 512 && lines >= kXcds / 2 * L ? (int)((lines + kXcds / 2 * L) / (kXcds * L)) : 0;
     return m;
 }
 
@@ -1306,8 +1310,8 @@ __device__ __forceinline__ long z_tile(const AxisMap& m)
 {
     const unsigned b = gridDim.x - 1 - blockIdx.x;
     if (__builtin_expect(m.run == 0, 1)) return m.first + b;
-    const unsigned run = (unsigned)m.run, group = 8 * run, g0 = b / group * group, r = b - g0;
-    return m.first + (g0 + group > gridDim.x ? b : g0 + r % 8 * run + r / 8);
+    const unsigned run = (unsigned)m.run, group = kXcds * run, g0 = b / group * group, r = b - g0;
+    return m.first + (g0 + group > gridDim.x ? b : g0 + r % kXcds * run + r / kXcds);
 }
 
 // ENERGY: the pass is the last one of an inverse transform psi = IFFT(c);
@@ -1615,7 +1619,8 @@ struct OrbitalRanges {
 // partial sums where it alone has read, in the first half of the runs of its
 // lines in its first orbital (float `line` of the run of element e), and
 // k_density_sum adds the ranges.  128 orbitals at 96^3 with a cutoff: the
-// density 346 us with one range, 252 with five.
+// density 346 us with one range, 252 with five; 234 now, with the twiddle copy
+// of its plane pass and the sums from the last butterfly.
 template <int N, int L, int MODE>
 __global__ void __launch_bounds__((AxisGeom<N, L>::T))
 k_axis_density(float2* buf, const float2* __restrict__ tw, AxisMap m, long vol,

@@ -10,9 +10,10 @@
 // tile as rows of x (pitch odd(nx)); their last stage writes rows of y (pitch
 // odd(ny)) for the y lines.  Nothing is prefetched: but for the largest planes
 // two workgroups or more share a compute unit and overlap.  Inverse + forward
-// in us, row and y passes -> this one: 16 x (100, 72, 90) 169 -> 138 (50 at the
-// copy rate), 200 x (24, 40, 30) 95 -> 70, 4 x (128, 125, 128) 134 -> 122, one
-// (20, 24, 18) 25.7 -> 21.3, 64 x (128, 8, 64) 69 -> 55.
+// in us, row and y passes -> this one, on buffers that change from call to call:
+// 16 x (100, 72, 90) 180 -> 145 (100 for two sweeps at the copy rate), 200 x
+// (24, 40, 30) 100 -> 76, 4 x (128, 125, 128) 140 -> 127, 64 x (128, 8, 64) 70 ->
+// 57, one (20, 24, 18) 28 -> 17 (a launch less, and less host time a call).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -20,9 +21,10 @@
 
 namespace fft3d {
 
-// Threads a plane and the points it may have, one class of planes each: as many
-// workgroups share a compute unit as the tile and 16 to 20 points a thread
-// allow (eight, eight, two and one at the largest plane of each class).
+// Threads a plane and the points it may have, one class of planes each: 8 to 20
+// points a thread, and ten, four, two and one workgroups on a compute unit:
+// registers leave 20, 16, 16 and 16 waves, the largest planes take 9, 34, 80
+// and 131 KB of LDS.
 struct RectClass {
     int threads, points;
 };

@@ -38,11 +38,18 @@ CubeFn cube_fn(int n, int sign);
 // has its twiddles as constants.
 CubeFn cube_lines_fn(int n, int sign);
 // Whether it takes a batch of n^3 grids (8 <= n <= 32) on `cus` compute units.
-// Up to 16 points k_cube has the same butterflies as the passes that a cutoff
-// prunes and is as fast until the device is full several times over (512 /
-// 1024 grids of 16^3, inverse + forward, 17.0 -> 15.0 / 26.4 -> 22.6 us); 18
-// and 20 always (one 20^3 grid 19.2 -> 13.8 us); 24 from a few grids on (single
-// ones differ little).  Above, one workgroup's whole grid takes longer than its
+// Whole grid against k_cube (up to 16 points) or the two passes, inverse +
+// forward, us.  Up to 16 points k_cube has the same butterflies as the passes
+// that a cutoff prunes (and so their bits), and the difference is small until
+// the device is full twice over: 16^3 x 64 8.6 / 8.5, x 256 11.2 / 12.3, x 512
+// 15.9 / 18.5, x 1024 26.5 / 28.1.  18 and 20 points always: one launch a
+// transform where the host is slower than the device (20^3 x 1 11.8 / 14.5, x
+// 64 13.6 / 16.3), although a few grids replayed from a graph take longer (x 1
+// 11.7 / 10.7).  24 points from 8 grids on: the device alone is faster from 32
+// on (called, x 1 15.9 / 12.9, x 8 16.3 / 14.6, x 32 16.9 / 15.9, x 64 17.8 /
+// 19.7; replayed, x 8 16.1 / 12.6, x 32 16.8 / 17.5, x 64 18.0 / 22.1); below 8 the
+// dense transform keeps the bits of the pruned one.  Above, one workgroup's whole
+// grid takes longer than its
 // planes spread over the device, until the batch fills a good part of it: 25^3
 // and 27^3 at 32 / 64 grids 0.91 / 1.15 times as fast as the passes, 30^3 at 64
 // / 96 grids 0.96 / 1.2 times, 32^3 at 64 / 96 0.92 / 1.02 times.  A 32^3 batch
