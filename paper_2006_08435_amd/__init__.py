@@ -46,6 +46,31 @@ def _stream_handle(stream=None) -> int:
     return _raw_stream(torch.cuda.current_device())
 
 
+def _lazy(*tensors) -> bool:
+    """Whether a tensor's conjugation or sign is still to be carried out: torch
+    keeps x.conj() as a flag on x's memory, which the kernels would read as it is."""
+    for t in tensors:
+        if t is not None and (t.is_conj() or t.is_neg()):
+            return True
+    return False
+
+
+def _on_plain(call, tensors, written, stream):
+    """call(*tensors, stream=stream) with lazy tensors replaced by plain copies,
+    made and, at the positions `written`, copied back in `stream`'s order."""
+    import contextlib
+    torch = _torch()
+    with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
+        made = {id(t): t.resolve_conj().resolve_neg() for t in tensors if _lazy(t)}
+        result = call(*[made.get(id(t), t) for t in tensors], stream=stream)
+        for t in (tensors[k] for k in written):
+            if id(t) in made:
+                t.copy_(made[id(t)])
+                if result is made[id(t)]:
+                    result = t
+    return result
+
+
 class Plan:
     """A planned batch of nx*ny*nz transforms (owns its device tables)."""
 
@@ -107,6 +132,8 @@ class Plan:
         """Gather the points inside the cutoff sphere: [batch, sphere_points]."""
         if packed is None:
             packed = self._packed_like(dense)
+        if _lazy(dense, packed):
+            return _on_plain(self.pack, (dense, packed), (1,), stream)
         self._check_pair(dense, packed)
         _lib.check(_lib.lib().fft3d_sphere_pack(self._h, dense.data_ptr(), packed.data_ptr(),
                                                 _stream_handle(stream)), "fft3d_sphere_pack")
@@ -117,6 +144,8 @@ class Plan:
         torch = _torch()
         if dense is None:
             dense = torch.empty(self.shape, dtype=packed.dtype, device=packed.device)
+        if _lazy(packed, dense):
+            return _on_plain(self.unpack, (packed, dense), (1,), stream)
         self._check_pair(dense, packed)
         _lib.check(_lib.lib().fft3d_sphere_unpack(self._h, packed.data_ptr(), dense.data_ptr(),
                                                   _stream_handle(stream)), "fft3d_sphere_unpack")
@@ -125,6 +154,8 @@ class Plan:
     def exec_packed(self, dense, packed, stream=None):
         """Pruned transform with a packed sphere: inverse packed -> dense;
         forward dense -> packed (``dense`` is overwritten as workspace)."""
+        if _lazy(dense, packed):
+            return _on_plain(self.exec_packed, (dense, packed), (0 if self.direction == FFT3D_INVERSE else 1,), stream)
         self._check_pair(dense, packed)
         _lib.check(_lib.lib().fft3d_exec_packed(self._h, dense.data_ptr(), packed.data_ptr(),
                                                 _stream_handle(stream)), "fft3d_exec_packed")
@@ -136,6 +167,8 @@ class Plan:
         torch = _torch()
         if out is None:
             out = torch.empty_like(c)
+        if _lazy(c, V, out, E, scale):
+            return _on_plain(self.apply_potential, (c, V, out, E, scale), (2, 3), stream)
         for t in (c, out, V):
             if not t.is_cuda or not t.is_contiguous():
                 raise ValueError("tensors must be contiguous device tensors")
@@ -152,6 +185,8 @@ class Plan:
             rho = torch.empty(self.shape[1:], dtype=torch.float32, device=c.device)
         if work is None:
             work = torch.empty_like(c)
+        if _lazy(c, occ, rho, work):
+            return _on_plain(self.density, (c, occ, rho, work), (2,), stream)
         for t in (c, occ, rho, work):
             if not t.is_cuda or not t.is_contiguous():
                 raise ValueError("tensors must be contiguous device tensors")
@@ -164,6 +199,8 @@ class Plan:
 
     def exec(self, inp, out=None, stream=None):
         """Transform device tensor ``inp`` into ``out`` (allocated if None)."""
+        if inp.is_conj() or (out is not None and out.is_conj()):
+            return _on_plain(self.exec, (inp, out), (1,), stream)
         if out is None:
             out = _torch().empty_like(inp)
         for t in (inp, out):
@@ -242,6 +279,11 @@ class PlanMany:
         torch = _torch()
         if outs is None:
             outs = [torch.empty_like(t) for t in ins]
+        if _lazy(*ins, *outs):
+            k = len(ins)
+            _on_plain(lambda *ts, stream: self.exec(ts[:k], ts[k:], stream), (*ins, *outs), range(k, k + len(outs)),
+                      stream)
+            return outs
         for (n, b), i, o in zip(self.groups, ins, outs):
             for t in (i, o):
                 if not t.is_cuda or not t.is_contiguous() or t.numel() != b * n ** 3 or t.dtype != torch.complex64:
@@ -297,6 +339,8 @@ class RealPlan:
         in_shape, out_shape = (self.real_shape, self.half_shape) if fwd else (self.half_shape, self.real_shape)
         if out is None:
             out = torch.empty(out_shape, dtype=out_dtype, device=inp.device)
+        if _lazy(inp, out):
+            return _on_plain(self.exec, (inp, out), (1,), stream)
         for t, dt, sh in ((inp, in_dtype, in_shape), (out, out_dtype, out_shape)):
             if not t.is_cuda or not t.is_contiguous() or t.dtype != dt or tuple(t.shape) != sh:
                 raise ValueError("expected a contiguous %s device tensor of shape %s" % (dt, sh))
@@ -358,7 +402,7 @@ def _transform(x, direction, out=None):
     torch = _torch()
     if x.dtype != torch.complex64:
         raise TypeError("fp32 path takes complex64 tensors")
-    x = x.contiguous()
+    x = x.contiguous()   # (a lazy conjugation stays; exec carries it out)
     if out is None and x.dim() == 3:   # one grid: no views of it
         nz, ny, nx = x.shape
         return get_plan(nx, ny, nz, 1, "fp32", direction).exec(x)
@@ -383,6 +427,8 @@ def quantize(x, precision="fp16", out=None, stream=None):
     torch = _torch()
     if x.dtype != torch.complex64 or not x.is_cuda:
         raise TypeError("quantize takes a complex64 device tensor")
+    if x.is_conj():
+        return _on_plain(lambda t, stream: quantize(t, precision, out, stream), (x,), (), stream)
     x = x.contiguous()
     C = int(x.shape[-1])
     rows = x.numel() // C

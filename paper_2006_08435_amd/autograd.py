@@ -52,7 +52,7 @@ def _check_energy_args(c, V):
     cb = c.unsqueeze(0) if c.dim() == 3 else c
     if cb.dim() != 4 or tuple(cb.shape[1:]) != tuple(V.shape):
         raise ValueError("c %s and V %s shapes differ" % (tuple(c.shape), tuple(V.shape)))
-    return cb.contiguous(), V.contiguous()
+    return cb.resolve_conj().contiguous(), V.resolve_neg().contiguous()
 
 
 class LocalPotentialEnergy(torch.autograd.Function):
@@ -88,7 +88,7 @@ class LocalPotentialEnergy(torch.autograd.Function):
             return None, None, None
         src, Vc = ctx.saved_tensors
         grad = torch.empty_like(src)
-        g64 = gE.detach().to(torch.float64).reshape(()).contiguous()
+        g64 = gE.detach().to(torch.float64).reshape(()).resolve_neg().contiguous()
         sh = _stream_handle()
         if ctx.have_psi:
             _lib.check(_lib.lib().fft3d_energy_vpsi_bwd(ctx.plan.handle, src.data_ptr(), g64.data_ptr(),
