@@ -233,7 +233,9 @@ int fft3d_exec_packed(fft3d_plan_t plan, void *dense, void *packed, fft3d_stream
  * decomposition).  fft3d_plan_passes returns how many; fft3d_exec_pass
  * enqueues pass `pass` alone (0-based), reading `in` and writing `out`, so a
  * profiler can time each kernel.  Running passes 0..k-1 in order with
- * in -> out for pass 0 and out -> out afterwards is exactly fft3d_exec.
+ * in -> out for pass 0 and out -> out afterwards gives exactly what fft3d_exec
+ * gives, and launches what it launches; only in place above 128 points a side
+ * the latter takes other kernels for the same bits (fft3d_plan).
  * Returns FFT3D_E_INVALID_ARG for a NULL plan/pointer or a pass out of range.
  */
 int fft3d_plan_passes(fft3d_plan_t plan);
