@@ -1065,7 +1065,7 @@ int fft3d_plan_describe(fft3d_plan_t p, char* buf, size_t len)
                  axis_str_info(p->nz).threads);
         d = tmp;
     } else if (p->passes.size() && p->passes[0].kind == Pass::kRectK) {
-        const KernelInfo a = rect_info(p->nx, p->ny), b = axis_str_info(p->nz);
+        const KernelInfo a = rect_info(p->nx, p->ny, p->passes[0].count), b = axis_str_info(p->nz);
         snprintf(tmp, sizeof tmp, "axes plane x=%d(%s) y=%d(%s) threads=%d lds=%d planes=%ld", p->nx,
                  radices(p->nx).c_str(), p->ny, radices(p->ny).c_str(), a.threads, a.lds_bytes, p->passes[0].count);
         d = tmp;

@@ -187,7 +187,7 @@ struct KernelInfo {
 };
 KernelInfo cube_info(int n);
 KernelInfo cube_lines_info(int n);
-KernelInfo rect_info(int nx, int ny);
+KernelInfo rect_info(int nx, int ny, long planes);
 KernelInfo split_plane_info(int n);
 KernelInfo split_z_info(int n);
 KernelInfo split_cols_info(int n);

@@ -515,7 +515,8 @@ def test_whole_grid_lines_of_10_and_12(F, n, b, sign):
 
 
 @pytest.mark.parametrize("shape,text", [
-    ((100, 72, 90), "axes plane x=100(10x10) y=72(12x6) threads=512 lds="),
+    ((100, 72, 90), "axes plane x=100(10x10) y=72(12x6) threads=1024 lds="),
+    ((100, 72, 270), "axes plane x=100(10x10) y=72(12x6) threads=512 lds="),
     ((128, 125, 1), "axes plane x=128(8x16) y=125(5x5x5) threads=1024 lds="),
     ((10, 4, 160), "axes plane x=10(10) y=4(4) threads=128 lds="),
     ((256, 256, 256), "axes split n=256 parts=4 plane(x 16x16, y 8x8, t1024, lds 131584) z(y 4, z 16x16, t1024, lds 133120)"),
@@ -577,3 +578,17 @@ def test_unpack_time_of_few_grids(F):
         packed = plan.pack(dense)
         return best_replay(lambda: plan.unpack(packed, dense))
     assert 5 * best(1) < best(16)
+
+
+@pytest.mark.parametrize("nx,ny", [(45, 25), (64, 60), (64, 81), (125, 80), (20, 16)])
+@pytest.mark.parametrize("planes", [255, 256, 257])
+def test_rectangular_planes_of_one_turn(F, nx, ny, planes):
+    """Twice the threads up to 256 planes; the same bits on both sides."""
+    x = workloads.uniform_grid((nx, ny, 1), 2300 + nx, batch=planes)
+    xt = torch.from_numpy(x).cuda()
+    plan = F.Plan(nx, ny, 1, planes, "fp32", FORWARD)
+    assert "plane x=" in plan.describe()
+    y = plan.exec(xt)
+    assert torch.equal(y, F.Plan(nx, ny, 1, 600, "fp32", FORWARD).exec(xt.repeat(3, 1, 1, 1)[:600].contiguous())[:planes])
+    for j in {0, planes - 1}:
+        assert rel(y[j].cpu().numpy(), oracle.fft3d(x[j].astype(np.complex128), FORWARD)) <= TOL
