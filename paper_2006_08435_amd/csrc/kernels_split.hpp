@@ -17,7 +17,8 @@
 // (k_split_y).  In place, copy of the input included, us, the three passes with
 // default radices -> these: 16 x 150^3 670 -> 623, 8 x 162^3 417 -> 375,
 // 12 x 160^3 557 -> 557, 4 x 256^3 761 -> 763, one 256^3 166.1 -> 168.5, one
-// 144^3 38.0 -> 38.9 (a third stage along y), one 135^3 44.1 -> 40.0; rows,
+// 144^3 38.0 -> 38.9 (a third stage along y; worst is one 180^3, alone and
+// replayed from a graph 54.2 -> 57.2), one 135^3 44.1 -> 40.0; rows,
 // k_split_y and k_split_z instead: 794, 500, 588, 820, 173.5, 43.6, 50.1.
 // Both passes hold one tile of up to 16384 points a compute unit, bound by HBM
 // and their barriers as k_plane_pf is.  Inverse + forward in us, three passes
