@@ -736,9 +736,11 @@ k_plane_pruned(const float2* in, float2* out, const float2* __restrict__ tw, lon
     // orbitals at 96^3 with a cutoff: the density 253 -> 245 us).  Measured and
     // not kept: two workgroups of 512 threads a compute unit without the
     // prefetch, where two tiles fit (80 to 100 points): 253 -> 287, its
-    // registers spill.
+    // registers spill.  Not where N divides 64: a wave then reads few whole
+    // groups of the table (91 x 32^3 pruned inverse + forward 31.2 us, with the
+    // copy 32.4; 610 x 32^3 102.3 and 104.5; 45^3 and up gain 2 to 17%).
     constexpr int TWN = Plan1D<N>::tw_len;
-    constexpr bool TWL = N % 64 != 0 && TWN > 0;
+    constexpr bool TWL = N % 64 != 0 && 64 % N != 0 && TWN > 0;
     __shared__ float2 tw_lds[TWL ? TWN : 1];
     if constexpr (TWL) {
         for (int i = tid; i < TWN; i += T) tw_lds[i] = tw[i];   // visible after the first barrier below
