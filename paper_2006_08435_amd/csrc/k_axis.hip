@@ -62,8 +62,12 @@ static hipError_t launch_axis_str_pruned(const float2* in, float2* out, const fl
     constexpr int T = AxisGeom<N, kAxisLines>::T;
     if (S > 0 && rows) return hipErrorInvalidValue;
     // inverse plans prune the loads (sphere-limited input), forward plans
-    // lines and stores (optionally scattering into a packed sphere)
-    return launch_tiles(in_runs(map, blocks, kAxisLines, false), blocks, [&](const AxisMap& m, unsigned grid) {
+    // lines and stores (optionally scattering into a packed sphere).  Forward
+    // tiles keep launch order: their lines outside the sphere are skipped, and
+    // runs of an eighth of a grid would leave the XCDs of the middle ones idle
+    // (forward to a packed sphere, us, launch order / runs: 92 x 75^3 169 / 203,
+    // 32 x 90^3 98 / 114, 20 x 81^3 55 / 64; inverse 32 x 90^3 87 / 82).
+    return launch_tiles(S > 0 ? in_runs(map, blocks, kAxisLines, false) : map, blocks, [&](const AxisMap& m, unsigned grid) {
         if constexpr (S < 0) {
             if (rows) {
                 hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, 3>), dim3(grid), dim3(T), 0, st, in, out, tw, m,

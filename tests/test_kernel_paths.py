@@ -461,7 +461,8 @@ def test_operator_in_runs_of_tiles(F, n, nz, b, cut):
 
 @pytest.mark.parametrize("n,nz,b", RUNS)
 def test_transforms_in_runs_of_tiles(F, n, nz, b):
-    """The dense, pruned and packed z passes, both signs, likewise."""
+    """The dense and pruned z passes, likewise; the pruned forward ones, which
+    keep launch order, with them."""
     r2, inside, c, _ = run_case(n, nz, b, True, False)
     full = workloads.uniform_grid((n, n, nz), 1700 + n, batch=b)
     psi = np.fft.ifftn(c.astype(np.complex128), axes=(1, 2, 3), norm="forward")
