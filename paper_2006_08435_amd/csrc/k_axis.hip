@@ -67,7 +67,8 @@ static hipError_t launch_axis_str_pruned(const float2* in, float2* out, const fl
     // runs of an eighth of a grid would leave the XCDs of the middle ones idle
     // (forward to a packed sphere, us, launch order / runs: 92 x 75^3 169 / 203,
     // 32 x 90^3 98 / 114, 20 x 81^3 55 / 64; inverse 32 x 90^3 87 / 82).
-    return launch_tiles(S > 0 ? in_runs(map, blocks, kAxisLines, false) : map, blocks, [&](const AxisMap& m, unsigned grid) {
+    const AxisMap order = S > 0 ? in_runs(map, blocks, kAxisLines, false) : map;
+    return launch_tiles(order, blocks, [&](const AxisMap& m, unsigned grid) {
         if constexpr (S < 0) {
             if (rows) {
                 hipLaunchKernelGGL((k_axis_str<N, S, kAxisLines, false, 3>), dim3(grid), dim3(T), 0, st, in, out, tw, m,
@@ -171,10 +172,14 @@ DensityFn axis_density_fn(int n)
     }
 }
 
-// Workgroups of the packed-sphere copies: one per plane, four waves where the
-// plane has more than two waves' worth of points; grid-stride beyond 2^20.
+// Workgroups of the packed-sphere copies: one per plane (grid-stride beyond
+// 2^20) of four waves, or of one for up to 128 points.  Where planes fill the
+// device several times over, one wave serves up to 320 points better, as four
+// have little to do each (unpack / pack us, replayed, four waves -> one: 587 x 15^3
+// 9.4 / 4.7 -> 7.5 / 4.7, 873 x 18^3 14.1 -> 10.1, 300 x 24^3 10.5 -> 9.2, 200 x 25^3
+// pack 6.1 -> 4.1; but 111 x 30^3, 450 pairs, 7.2 -> 8.2).
 static dim3 sphere_grid(long planes) { return dim3((unsigned)(planes < (1L << 20) ? planes : (1L << 20))); }
-static dim3 sphere_block(long points) { return dim3(points > 128 ? 256 : 64); }
+static dim3 sphere_block(long planes, long points) { return dim3(points > (planes >= 2048 ? 320 : 128) ? 256 : 64); }
 // Workgroups that share a plane of `units` units: as many as make 2048 of them
 // in all, eight a compute unit, with a unit or more a thread.  With one a plane
 // two grids of 125^3 took 30.4 us and one of 128^3 17.4, so 10.6 and 7.6 (one
@@ -190,8 +195,9 @@ hipError_t launch_sphere_pack(const float2* src, float2* dst, const SphereRow* r
 {
     const long planes = batch * nzp;
     if (planes <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sphere_pack, sphere_grid(planes), sphere_block((long)ax.count() * ay.count()), 0, st, src,
-                       dst, rows, npts, zlist, nzp, nz, ax, ay, planes);
+    const dim3 block = sphere_block(planes, (long)ax.count() * ay.count());
+    hipLaunchKernelGGL(k_sphere_pack, sphere_grid(planes), block, 0, st, src, dst, rows, npts, zlist, nzp, nz, ax, ay,
+                       planes);
     return hipGetLastError();
 }
 
@@ -199,14 +205,13 @@ hipError_t launch_sphere_unpack(const float2* src, float2* dst, const SphereRow*
                                 int nx, double R2, long batch, hipStream_t st)
 {
     const long planes = batch * nz, units = (long)ny * nx / (nx % 2 == 0 ? 2 : 1);
+    const dim3 block = sphere_block(planes, units);
     dim3 grid = sphere_grid(planes);
     grid.y = sphere_parts(planes, units);
     if (nx % 2 == 0)   // every row, so every plane, starts on 16 bytes
-        hipLaunchKernelGGL(k_sphere_unpack<2>, grid, sphere_block(units), 0, st, src, dst, rows, npts, nz, ny, nx, R2,
-                           planes);
+        hipLaunchKernelGGL(k_sphere_unpack<2>, grid, block, 0, st, src, dst, rows, npts, nz, ny, nx, R2, planes);
     else
-        hipLaunchKernelGGL(k_sphere_unpack<1>, grid, sphere_block(units), 0, st, src, dst, rows, npts, nz, ny, nx, R2,
-                           planes);
+        hipLaunchKernelGGL(k_sphere_unpack<1>, grid, block, 0, st, src, dst, rows, npts, nz, ny, nx, R2, planes);
     return hipGetLastError();
 }
 
@@ -216,8 +221,8 @@ static hipError_t launch_axis_row(const float2* in, float2* out, const float2* t
     const long blocks = (rows + kRowLines - 1) / kRowLines;
     return launch_blocks(blocks, [&](long first, unsigned grid) {
         const long r0 = first * kRowLines;
-        hipLaunchKernelGGL((k_axis_row<N, S, kRowLines>), dim3(grid), dim3(RowGeom<N, kRowLines>::T), 0, st, in + r0 * N,
-                           out + r0 * N, tw, rows - r0);
+        hipLaunchKernelGGL((k_axis_row<N, S, kRowLines>), dim3(grid), dim3(RowGeom<N, kRowLines>::T), 0, st,
+                           in + r0 * N, out + r0 * N, tw, rows - r0);
     });
 }
 

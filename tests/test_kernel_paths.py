@@ -535,7 +535,8 @@ def test_describe_names_the_kernels_that_run(F, shape, text):
 
 
 @pytest.mark.parametrize("n,nz,b,r2", [(24, 2, 1, 36.0), (32, 1, 1, 1e9), (125, 3, 1, 900.0), (128, 8, 2, 900.0),
-                                       (16, 3, 683, 16.0), (30, 5, 409, 30.0), (30, 5, 410, 30.0)])
+                                       (16, 3, 683, 16.0), (30, 5, 409, 30.0), (30, 5, 410, 30.0), (15, 3, 682, 30.0),
+                                       (15, 3, 700, 1e9), (18, 4, 512, 40.0), (25, 3, 700, 60.0)])
 def test_unpack_planes_shared_by_workgroups(F, n, nz, b, r2):
     """Few planes (many workgroups each, the last ones with fewer units) to
     more than 2048 (one each): bit for bit."""
@@ -546,8 +547,10 @@ def test_unpack_planes_shared_by_workgroups(F, n, nz, b, r2):
     plan = F.Plan(n, n, nz, b, "fp32", INVERSE)
     plan.set_cutoff(r2)
     dense = torch.full((b, nz, n, n), complex("nan"), dtype=torch.complex64, device="cuda")
-    got = plan.unpack(torch.from_numpy(np.ascontiguousarray(x[:, inside])).cuda(), dense).cpu().numpy()
+    packed = torch.from_numpy(np.ascontiguousarray(x[:, inside])).cuda()
+    got = plan.unpack(packed, dense).cpu().numpy()
     assert np.array_equal(got.view(np.uint64), np.where(inside[None], x, np.complex64(0)).view(np.uint64))
+    assert torch.equal(plan.pack(torch.from_numpy(x).cuda()), packed)
 
 
 def best_replay(call, calls=10):
